@@ -176,7 +176,10 @@ lutgemm_status_t lutgemm_table_offsets(const lutgemm_problem_t *problem, int64_t
  * leaves them zero again (the kernel re-arms them) and nothing else is ever stored
  * there, so one zero fill per allocation suffices even when the workspace is shared
  * by calls on different problems.  A workspace must not be shared by calls that
- * run concurrently.
+ * run concurrently.  With several tokens (ACT_FP16, M >= 16, see
+ * lutgemm_mpgemm) the size covers the matrix-core evaluation (its prepared activations and partial sums); a smaller
+ * workspace that still holds the lookup kernels' partial sums (none, if those do not
+ * split K) is accepted and runs the lookup kernels.
  */
 size_t lutgemm_workspace_size(const lutgemm_problem_t *problem, int64_t M);
 
@@ -229,6 +232,12 @@ lutgemm_status_t lutgemm_precompute(const lutgemm_problem_t *problem, int64_t M,
  *   workspace  device, workspace_bytes >= lutgemm_workspace_size(problem, M);
  *              may be NULL when that size is 0
  * FP path: O = t_m sum_q s'_q (sum_b 2^b sum_j L_{b,j} - z'_q S_q), FP32.
+ * With several tokens (ACT_FP16; UINT weights with group scales: M >= 16 and M N <= 2^24;
+ * other UINT weights of 2 or 4 bits: 16 <= M <= 64, or M >= 16 and M N <= 2^20; other
+ * weights: 16 <= M <= 32) the sums of lookups are evaluated on the matrix cores: an entry
+ * is a signed sum of its 4 activations (Eq. 5), so the lookups of a column add up to the
+ * dot product of its codes with the activations, which are recovered from the tables.
+ * The tables must be half tables as the layout defines.
  * INT8 path: acc = sum_k q_a w exactly; O = acc (INT32) or (float(acc) s_a) s_w.
  * TERNARY_3IN5: O = t_m s (sum_j L_j) (FP path, FP32) with one lookup per triple.
  * The result is bitwise reproducible run to run.
@@ -244,12 +253,13 @@ lutgemm_status_t lutgemm_mpgemm(const lutgemm_problem_t *problem, int64_t M, con
 /*
  * lutgemm_mpgemm without a workspace argument, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses that
- * forbid allocation).  Same arguments, kernels and results as lutgemm_mpgemm; the
+ * forbid allocation).  Same arguments, kernels and results as lutgemm_mpgemm (with
+ * several tokens, as lutgemm_mpgemm on a workspace of the array's size); the
  * K-split partial sums go to a static device array of
  * LUTGEMM_NOALLOC_SCRATCH_BYTES per GPU that the library holds until the process
  * ends (its address is looked up on the first call with each device current; it
  * is zero when the library is loaded and every call leaves it zeroed).
- * Calls needing more scratch than that (lutgemm_workspace_size) return
+ * Calls whose lookup kernels need more scratch than that return
  * LUTGEMM_ERROR_NOT_SUPPORTED and launch nothing, with the sizes in
  * lutgemm_last_error().  No call allocates or frees memory.  All calls on one GPU
  * share its array: calls that overlap on one GPU (other streams, other threads)
@@ -279,17 +289,18 @@ size_t lutgemm_fused_workspace_size(const lutgemm_problem_t *problem, int64_t M)
  * activations as given (no token scaling, no FP16 rounding of entries), plus the
  * split sum; with larger weights and ACT_INT8 the same kernel, each workgroup
  * reading the whole token for the absmax and building the exact INT16 entries of
- * the precompute's quantization for its K range.  Several tokens (2 < M <= 64) with ACT_FP16 on layers of at most
- * 64 x 256 columns: the multi-token kernel reads the FP16 activations of its
- * tokens and K range, scales each token by the power of two 2^-e with e from its
- * absmax over that K range, and builds the same FP16 entries as
- * lutgemm_precompute (tuning key LUTGEMM_TUNE_MT_FUSED forces it on or off; every
- * column tile repeats the build, so beyond those sizes precompute + mpGEMM is
- * faster).  TERNARY_3IN5: one kernel for every M, tables built per workgroup for
- * its token.  Otherwise (larger M or N with ACT_FP16, ACT_INT8 with M > 2,
- * ACT_FP16_LUT8) it runs lutgemm_precompute into the workspace followed by
- * lutgemm_mpgemm: with several tokens every workgroup would have to read all of its
- * tokens for the INT8 quantizer's absmax.
+ * the precompute's quantization for its K range.  Several tokens with ACT_FP16: the calls
+ * that lutgemm_mpgemm evaluates on the matrix cores run there on the activations
+ * themselves (codes and activations are exact in FP16, scales and zero points are applied
+ * in FP32); else, with 2 < M <= 64 on layers of at most 64 x 256 columns, the multi-token kernel reads the FP16 activations
+ * of its tokens and K range, scales each token by the power of two 2^-e with e from its
+ * absmax over that K range, and builds the same FP16 entries as lutgemm_precompute
+ * (tuning key LUTGEMM_TUNE_MT_FUSED forces it on or off; every column tile repeats the
+ * build, so beyond those sizes precompute + mpGEMM is faster).  TERNARY_3IN5: one kernel
+ * for every M, tables built per workgroup for its token.  Otherwise (larger N with
+ * ACT_FP16, ACT_INT8 with M > 2, ACT_FP16_LUT8) it runs lutgemm_precompute into the
+ * workspace followed by lutgemm_mpgemm: with several tokens every workgroup would have to
+ * read all of its tokens for the INT8 quantizer's absmax.
  *   act        device FP16 [M][K]
  *   packed, out, out_dtype, accumulate   as for lutgemm_mpgemm
  *   workspace  device, workspace_bytes >= lutgemm_fused_workspace_size(problem, M);
@@ -298,9 +309,9 @@ size_t lutgemm_fused_workspace_size(const lutgemm_problem_t *problem, int64_t M)
  * lutgemm_mpgemm.  FP16 activations: the zero-point term is summed per 128-block
  * instead of per quantization group, and the split-K kernel's entries are not
  * rounded to FP16, so results agree with the two-call path to within that
- * rounding (TERNARY_3IN5, and the multi-token kernel on weights without zero
- * points: bitwise, unless an entry or partial sum is subnormal).  Bitwise
- * reproducible run to run.
+ * rounding (TERNARY_3IN5, and the multi-token lookup kernel on weights without zero
+ * points: bitwise, unless an entry or partial sum is subnormal; on the matrix cores the
+ * fused call has no table rounding at all).  Bitwise reproducible run to run.
  */
 lutgemm_status_t lutgemm_mpgemm_fused(const lutgemm_problem_t *problem, int64_t M, const void *act,
                                       const void *packed, void *out, int32_t out_dtype,
@@ -388,7 +399,14 @@ enum {
                                        integer (INT8 activations, or FP16 activations on weights with
                                        one scale per column or tensor); 0 always sums FP32 partials
                                        in split order (1)                                            */
-    LUTGEMM_TUNE_COUNT = 17
+    LUTGEMM_TUNE_MFMA = 17,         /* LUTGEMM_MFMA: several tokens (M > 2, ACT_FP16) on the matrix
+                                       cores: 0 never (the lookup kernels), 1 always (-1: planned;
+                                       also off while a key of the multi-token lookup kernel, MT_* or
+                                       MT4 / MT16, is away from its default)                        */
+    LUTGEMM_TUNE_MFMA_TILE = 18,    /* LUTGEMM_MFMA_TILE: tokens per workgroup there, 32, 64 or 128
+                                       (0: planned)                                                  */
+    LUTGEMM_TUNE_MFMA_SPLITS = 19,  /* LUTGEMM_MFMA_SPLITS: K splits there (0: planned)              */
+    LUTGEMM_TUNE_COUNT = 20
 };
 
 /* Sets planner override `key` (LUTGEMM_TUNE_*) to `value` (-1: its default).

@@ -74,8 +74,8 @@ const char *const kTuneEnv[LUTGEMM_TUNE_COUNT] = {
     "LUTGEMM_SPLITS",        "LUTGEMM_KBS",           "LUTGEMM_MT16",      "LUTGEMM_MT_TARGET",
     "LUTGEMM_MT_SPLITS",     "LUTGEMM_MT_ORDER",      "LUTGEMM_DEQUANT_KIND", "LUTGEMM_LOG",
     "LUTGEMM_SPLIT_PRE",     "LUTGEMM_DEQUANT_SPLITS", "LUTGEMM_MT_FUSED", "LUTGEMM_MT4",
-    "LUTGEMM_SPLIT_EXACT"};
-const int kTuneDefault[LUTGEMM_TUNE_COUNT] = {256, 10000, -1, -1, 0, 0, 1, 8, 0, -1, -1, 0, -1, 0, -1, 1, 1};
+    "LUTGEMM_SPLIT_EXACT",   "LUTGEMM_MFMA",          "LUTGEMM_MFMA_TILE", "LUTGEMM_MFMA_SPLITS"};
+const int kTuneDefault[LUTGEMM_TUNE_COUNT] = {256, 10000, -1, -1, 0, 0, 1, 8, 0, -1, -1, 0, -1, 0, -1, 1, 1, -1, 0, 0};
 std::atomic<int> g_tune[LUTGEMM_TUNE_COUNT];
 
 bool tune_value_ok(int key, int value) {
@@ -326,6 +326,69 @@ LutPlan plan_lut(const Layout &L, int64_t M, bool fused) {
     return P;
 }
 
+// Which FP16 calls go to the matrix cores.  They win from 16 tokens on (graph replays, us,
+// lookups -> matrix cores: INT4 4096 x 12288 33 -> 20 at M = 16, 273 -> 60 at 256, 1004 ->
+// 151 at 1024; the smallest gain, INT4 11008 x 300 two-call at 16 tokens, 22.4 -> 21.3; at 8
+// tokens three launches against two lose on small layers, INT4 4096 x 1024 12.1 -> 13.0).
+// They are also the more exact path, by so much that a call's result would move: the lookup
+// kernel's FP16 word sums are off by 4.6-7.6e-4 (relative), and over many outputs with one
+// scale per column or tensor, where no group scales average them, its largest deviation
+// exceeds 1e-2 of the output's rms (24 seeds each, deviations over 1e-2: binary 8192 columns
+// 0 / 0 / 1 / 6 at 16 / 32 / 64 / 256 tokens; ternary 0 / 0 / 1 / 3; INT2 per channel 0 up to
+// 64, 2 at 256; INT4 and INT2 groups of 128 at most 1 up to 2^24 outputs).  A caller that
+// compares with stored results must not see more than that from a choice of kernel, so
+// larger calls of those kinds stay with the lookups.
+static bool mfma_planned(const Layout &L, int64_t M) {
+    if (M < 16) return false;
+    if (L.wfmt == LUTGEMM_WFMT_UINT && L.Q > 1) return M * L.N <= (int64_t)1 << 24;
+    if (L.bits > 1 && L.wfmt == LUTGEMM_WFMT_UINT) return M <= 64 || M * L.N <= (int64_t)1 << 20;
+    return M <= 32;
+}
+
+// Tile (tokens per workgroup) of the matrix-core plan: a larger one decodes each weight for
+// more tokens, a smaller one gives more workgroups.  With group scales (the dearer decode)
+// 128 tokens win from 192 such tiles on and 64 from 96 (INT4 4096 x 12288, tiles of 32 / 64 /
+// 128: 44 / 39 / 46 us at M = 128, 97 / 95 / 93 at 512); without, from 512 and 512 (binary:
+// 62 / 68 / 81 at 512, 113 / 106 / 123 at 1024).  K is split to two workgroups per CU, at
+// least 4 blocks each.
+LutPlan plan_mfma(const Layout &L, int64_t M) {
+    LutPlan P{};
+    P.kind = -1;
+    const int force = tuning(LUTGEMM_TUNE_MFMA);
+    if (L.act != LUTGEMM_ACT_FP16 || L.tri || M <= 2 || force == 0) return P;
+    // overrides of the multi-token lookup kernel select that kernel
+    if (force < 0) {
+        if (!mfma_planned(L, M)) return P;
+        for (const int key : {LUTGEMM_TUNE_MT16, LUTGEMM_TUNE_MT_TARGET, LUTGEMM_TUNE_MT_SPLITS, LUTGEMM_TUNE_MT_ORDER,
+                              LUTGEMM_TUNE_MT_FUSED, LUTGEMM_TUNE_MT4})
+            if (tuning(key) != kTuneDefault[key]) return P;
+    }
+    P.kind = 4;
+    P.n_tiles = L.N_pad / NTILE;
+    auto tiles = [&](int mt) { return P.n_tiles * ((M + mt - 1) / mt); };
+    const bool grp = L.Q > 1;
+    P.mt = tiles(128) >= (grp ? 192 : 512) ? 128 : tiles(64) >= (grp ? 96 : 512) ? 64 : 32;
+    if (M <= 64 && P.mt == 128) P.mt = 64;
+    if (M <= 32) P.mt = 32;
+    const int tile = tuning(LUTGEMM_TUNE_MFMA_TILE);
+    if (tile == 32 || tile == 64 || tile == 128) P.mt = tile;
+    P.m_tiles = (M + P.mt - 1) / P.mt;
+    const int64_t base = P.n_tiles * P.m_tiles, target = 2 * tuning(LUTGEMM_TUNE_TARGET_BLOCKS);
+    int64_t splits = base < target ? target / base : 1;
+    const int64_t max_splits = L.KB / 4 > 1 ? L.KB / 4 : 1;
+    if (splits > max_splits) splits = max_splits;
+    const int fs = tuning(LUTGEMM_TUNE_MFMA_SPLITS);
+    if (fs > 0) splits = fs < L.KB ? fs : L.KB;
+    P.kbs = (int)((L.KB + splits - 1) / splits);
+    P.splits = (int)((L.KB + P.kbs - 1) / P.kbs);
+    P.order = 8;
+    P.part_off = CNT_AREA;
+    P.prep_off = CNT_AREA + (P.splits > 1 ? align256((size_t)P.splits * P.m_tiles * P.mt * L.N_pad * 4) : 0);
+    P.prep_s_off = P.prep_off + align256((size_t)P.m_tiles * P.mt * L.K * 2);  // whole token tiles
+    P.ws_bytes = P.prep_s_off + align256((size_t)M * L.Q * 4);
+    return P;
+}
+
 }  // namespace lutgemm
 
 namespace lutgemm {
@@ -370,6 +433,22 @@ static LutParams lut_params(const Layout &L, const LutPlan &plan, int64_t M, con
     return lp;
 }
 
+// One matrix-core call on tables (T != NULL) or activations: prepare, multiply, sum the splits.
+static lutgemm_status_t run_mfma(const Layout &L, const LutPlan &plan, int64_t M, const void *tables, const void *act,
+                                 const void *packed, void *out, int32_t out_dtype, int32_t accumulate, void *workspace,
+                                 void *stream) {
+    char *ws = (char *)workspace;
+    LutParams lp = lut_params(L, plan, M, tables, packed, out, out_dtype, accumulate, workspace);
+    lp.act = (const uint16_t *)act;
+    float *S = L.wfmt != LUTGEMM_WFMT_BINARY ? (float *)(ws + plan.prep_s_off) : nullptr;
+    int e = launch_mfma_prep(lp, L, ws + plan.prep_off, S, stream);
+    lp.act = (const uint16_t *)(ws + plan.prep_off);
+    lp.S = S;
+    if (e == 0) e = launch_mfma(lp, L, plan, stream);
+    if (e == 0 && plan.splits > 1) e = launch_finalize(lp, L, plan, stream);
+    return hip_error(e);
+}
+
 static void log_plan(const char *who, const Layout &L, const LutPlan &plan, int64_t M) {
     std::fprintf(stderr, "%s: M=%lld K=%lld N=%lld b=%d kind=%d cfg=%d kbs=%d splits=%d mt=%d grid=%lldx%dx%lld\n",
                  who, (long long)M, (long long)L.K, (long long)L.N, L.bits, plan.kind, plan.gemv_cfg,
@@ -384,6 +463,13 @@ struct FusedScratch {
     bool fused;
     size_t tables, tables_off, tok_off, total;
 };
+
+// Scratch of lutgemm_mpgemm: what the planned kernels need, and at least what the lookup
+// kernels need (they run on a workspace too small for the matrix-core path).
+static size_t lut_ws_bytes(const Layout &L, int64_t M) {
+    const size_t lookup = plan_lut(L, M).ws_bytes, mfma = plan_mfma(L, M).ws_bytes;
+    return lookup > mfma ? lookup : mfma;
+}
 
 static FusedScratch fused_scratch(const Layout &L, const LutPlan &plan, int64_t M) {
     FusedScratch f{};
@@ -468,10 +554,17 @@ lutgemm_status_t lutgemm_table_offsets(const lutgemm_problem_t *problem, int64_t
     return LUTGEMM_SUCCESS;
 }
 
+}  // extern "C"
+
+size_t lutgemm::min_workspace(const lutgemm_problem_t *problem, int64_t M) {
+    return plan_lut(make_layout(*problem), M).ws_bytes;
+}
+
+extern "C" {
+
 size_t lutgemm_workspace_size(const lutgemm_problem_t *problem, int64_t M) {
     if (check_problem(problem, M) != LUTGEMM_SUCCESS) return 0;
-    Layout L = make_layout(*problem);
-    return plan_lut(L, M).ws_bytes;
+    return lut_ws_bytes(make_layout(*problem), M);
 }
 
 lutgemm_status_t lutgemm_pack_weights(const lutgemm_problem_t *problem, const void *codes,
@@ -541,6 +634,11 @@ lutgemm_status_t lutgemm_mpgemm(const lutgemm_problem_t *problem, int64_t M, con
     if (out_dtype == LUTGEMM_OUT_INT32 && problem->act != LUTGEMM_ACT_INT8) return LUTGEMM_ERROR_NOT_SUPPORTED;
     if (accumulate != 0 && accumulate != 1) return LUTGEMM_ERROR_INVALID_VALUE;
     Layout L = make_layout(*problem);
+    const LutPlan mp = plan_mfma(L, M);
+    if (mp.kind == 4 && workspace && aligned16(workspace) && workspace_bytes >= mp.ws_bytes) {
+        if (tuning(LUTGEMM_TUNE_LOG)) log_plan("lutgemm_mpgemm", L, mp, M);
+        return run_mfma(L, mp, M, tables, nullptr, packed, out, out_dtype, accumulate, workspace, stream);
+    }
     LutPlan plan = plan_lut(L, M);
     if (plan.ws_bytes > 0) {
         if (!workspace || !aligned16(workspace)) return LUTGEMM_ERROR_INVALID_VALUE;
@@ -554,7 +652,12 @@ lutgemm_status_t lutgemm_mpgemm(const lutgemm_problem_t *problem, int64_t M, con
 size_t lutgemm_fused_workspace_size(const lutgemm_problem_t *problem, int64_t M) {
     if (check_problem(problem, M) != LUTGEMM_SUCCESS) return 0;
     Layout L = make_layout(*problem);
-    return fused_scratch(L, plan_lut(L, M, true), M).total;
+    const FusedScratch fs = fused_scratch(L, plan_lut(L, M, true), M);
+    const size_t mfma = plan_mfma(L, M).ws_bytes;
+    if (mfma == 0) return fs.total;
+    // (the precompute + mpGEMM form: its tables come after the whole workspace)
+    if (!fs.fused) return align256(lut_ws_bytes(L, M)) + fs.tables;
+    return fs.total > mfma ? fs.total : mfma;
 }
 
 lutgemm_status_t lutgemm_mpgemm_fused(const lutgemm_problem_t *problem, int64_t M, const void *act,
@@ -569,6 +672,11 @@ lutgemm_status_t lutgemm_mpgemm_fused(const lutgemm_problem_t *problem, int64_t 
     if (out_dtype == LUTGEMM_OUT_INT32 && problem->act != LUTGEMM_ACT_INT8) return LUTGEMM_ERROR_NOT_SUPPORTED;
     if (accumulate != 0 && accumulate != 1) return LUTGEMM_ERROR_INVALID_VALUE;
     Layout L = make_layout(*problem);
+    const LutPlan mp = plan_mfma(L, M);
+    if (mp.kind == 4 && workspace && aligned16(workspace) && workspace_bytes >= mp.ws_bytes) {
+        if (tuning(LUTGEMM_TUNE_LOG)) log_plan("lutgemm_mpgemm_fused", L, mp, M);
+        return run_mfma(L, mp, M, nullptr, act, packed, out, out_dtype, accumulate, workspace, stream);
+    }
     LutPlan plan = plan_lut(L, M, true);
     FusedScratch fs = fused_scratch(L, plan, M);
     if (fs.total > 0) {

@@ -1,0 +1,354 @@
+// Several tokens on the matrix cores (LUT Tensor Core, Section 3.1 with Eq. 2-6).
+//
+// A half table is linear in its four activations (Eq. 5: every entry is a signed sum of
+// them), so the lookups of one column over K add up to the dot product of the activations
+// with the reinterpreted codes (Eq. 2).  With several tokens that sum is a contraction,
+// and v_mfma_f32_32x32x16_f16 evaluates it from the same packed bit-planes without
+// materializing an entry: the codes are exact in FP16, every product is exact in FP32,
+// and scale and zero point are applied in FP32 (Eq. 3), so the result is closer to the
+// exact product than the lookups in FP16 tables.
+//
+// The weight codes.  The k order inside an MFMA is free as long as both operands follow
+// it, so it is chosen to make the decode cheap.  Lane (c, g) = (lane % 32, lane / 32) of a
+// 32-column block takes words 2 g and 2 g + 1 of column c's 16-byte plane word.  After the
+// Eq. 6 inversion is undone on whole words, bits s and s + 16 of a word (one shift, one
+// three-input bit operation) become an FP16 pair: +-1 for one plane; for b planes, whose
+// bits are first interleaved into b-bit fields, 1 + q / 2^b (the field in the top mantissa
+// bits of 1.0).  Bit s is activation 4 (s / 4) + 3 - s % 4 of the word, so MFMA step (j, t)
+// of a lane holds, in register e, activations 4 t + e (low half) and 4 t + e + 16 (high
+// half) of word 2 g + j.  The activations come permuted to that order ("prepared") by
+// prep_kernel, once per call.
+//
+// The weight value is w = sc (v - zo) in terms of the FP16 value v (b = 1: v = +-1, sc = s',
+// zo = z' of Eq. 2; else sc = 2^b s, zo = 1 + z / 2^b): the sum over a quantization group is
+// sc (sum v x - zo S) with S the group's activation sum.
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+
+#include "lut_common.h"
+#include "mfma_common.h"
+
+namespace lutgemm {
+
+// ---------------------------------------------------------------- prepared activations
+
+// One token per workgroup, 32 activations per lane and step: permuted to the MFMA order, and
+// (S != NULL) summed over each quantization group in FP32 in a fixed order: the 32 of a lane,
+// the 4 lanes of a 128-block, then the blocks of the group by one wavefront.
+// TAB: the activations of table-fed calls, from the half tables themselves: the 8 entries of
+// a group are a full two-level design in x1, x2, x3 with -x0 in all of them, so
+// x_e = (1/8) sum_i (sign of x_e in entry i) T[i] is the least-squares solution (exact when
+// the entries are; the rounding errors of the 8 FP16 entries average out, mostly below half
+// an ulp of the activation, which rounding back to FP16 then restores).  S is the sum of
+// these activations, not the table buffer's: what is left of the entries' errors then enters
+// the result multiplied by the weight, as in the lookups, not by the decoded value.
+template <bool TAB>
+__global__ __launch_bounds__(256) void prep_kernel(const void *src, uint4 *dst, float *S, int64_t K, int Q, int kpg) {
+    extern __shared__ float bs[];  // K / 128 block sums when S
+    const int64_t m = blockIdx.x;
+    uint4 *d = dst + m * (K / 8);
+    for (int64_t w = threadIdx.x; w < K / 32; w += blockDim.x) {
+        uint4 x[4];
+        if constexpr (TAB) {
+            const uint4 *T = (const uint4 *)src + m * (K / 4) + 8 * w;
+            uint4 e[8];
+#pragma unroll
+            for (int g = 0; g < 8; ++g) e[g] = T[g];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint2 lo = table_acts(e[2 * i]), hi = table_acts(e[2 * i + 1]);
+                x[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+        } else {
+            const uint4 *a = (const uint4 *)((const uint16_t *)src + m * K) + 4 * w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = a[i];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[4 * w + t] = mfma_chunk(x, t);
+        if (S) {
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t h[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s = (s + h2f(h[j] & 0xFFFFu)) + h2f(h[j] >> 16);
+            }
+            s += __shfl_xor(s, 1, 64);  // (K % 128 == 0: the 4 lanes of a block are live together)
+            s += __shfl_xor(s, 2, 64);
+            if ((w & 3) == 0) bs[w >> 2] = s;
+        }
+    }
+    if (!S) return;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    if (kpg == 1) {
+        for (int q = threadIdx.x; q < Q; q += blockDim.x) S[m * Q + q] = bs[q];
+        return;
+    }
+    for (int q = wave; q < Q; q += waves) {
+        float s = 0.f;
+        for (int b = lane; b < kpg; b += 64) s += bs[q * kpg + b];
+        s = wave_sum_f(s);
+        if (lane == 63) S[m * Q + q] = s;
+    }
+}
+
+// ---------------------------------------------------------------- large M
+//
+// Workgroup tile 32 MS (tokens) x 256 (columns), 4 wavefronts of 32 MS x 64, K step one
+// 128-block.  MS = 4: 128 accumulators per lane, two workgroups per CU, so that one
+// wavefront of a SIMD decodes or scales while the other drives the matrix cores.  The
+// weights never pass through LDS: each lane decodes the operand registers of its own
+// column from 8 bytes per plane.  The prepared activations stream straight into LDS
+// (global_load_lds_dwordx4, two buffers, one barrier per step); 16-byte chunk c of row r
+// sits at slot c ^ (r % 16) of the row's 256 bytes, so the operand reads of 16 consecutive
+// rows cover all banks.
+typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void glb_void;
+
+template <int BITS, bool GRP, int MS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void mfma_gemm_kernel(LutParams p, int wfmt, uint32_t n_tiles, uint32_t m_tiles, int order) {
+    constexpr int ROWS = 32 * MS;
+    constexpr int CP = GRP ? 2 : 4, NP = 8 / CP;  // MFMAs per part of a chain, parts per chain
+    __shared__ __attribute__((aligned(16))) char A0[ROWS * 256], A1[ROWS * 256];
+    __shared__ __attribute__((aligned(16))) char Es[MS == 1 ? 16384 : 16];
+    char *E = MS == 1 ? Es : A0;  // 4 KiB per wavefront for the epilogue
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 31, lg = lane >> 5;
+    const MTile tl = mfma_tile(blockIdx.x, n_tiles, m_tiles, order);
+    const int64_t m0 = (int64_t)tl.mt * ROWS;
+    const uint32_t n0 = tl.nt * NTILE + wave * 64 + lc;  // column of n-sub 0 (n-sub 1: + 32)
+    const int kbA = tl.split * p.kbs;
+    const int kbB = kbA + p.kbs < (int)p.KB ? kbA + p.kbs : (int)p.KB;
+
+    floatx16_t acc[MS][2];
+#pragma unroll
+    for (int i = 0; i < MS; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // activations of block kb into dst: each instruction fills 4 rows (1 KiB); the tile's
+    // rows past M are scratch (their sums are never stored)
+    const uint32_t rowb = (uint32_t)p.K * 2u;
+    const __amdgpu_buffer_rsrc_t rA = buf_rsrc((const char *)p.act + m0 * p.K * 2, ROWS * rowb);
+    const uint32_t avo = (uint32_t)(lane >> 4) * rowb + 16u * (uint32_t)((lane & 15) ^ (lane >> 4));  // (rowb % 256 = 0)
+    auto load_act = [&](int kb, char *dst) {
+#pragma unroll
+        for (int i = 0; i < 2 * MS; ++i) {
+            const int row0 = wave * 8 * MS + 4 * i;  // row0 % 16 = 4 (row0 / 4 % 4)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void *)(dst + row0 * 256), 16, (int)(avo ^ (64u * ((2 * MS * wave + i) & 3))),
+                                                     (int)((uint32_t)row0 * rowb + (uint32_t)kb * 256u), 0, 0);
+        }
+    };
+    int q_cur = GRP ? kbA / p.kpg : 0;  // quantization group of the last block loaded
+    struct W {
+        uint2 w[BITS];
+        uint32_t m;
+    };
+    // words and metadata of n-sub j of block kb
+    auto load_w = [&](int kb, int j, W &w) {
+        const __amdgpu_buffer_rsrc_t rW =
+            buf_rsrc(p.planes + (int64_t)kb * BITS * p.N_pad, (uint32_t)BITS * (uint32_t)p.N_pad * 16u);
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) w.w[t] = buf_u64(rW, n0 * 16u + 8u * lg + 512u * j, (uint32_t)t * (uint32_t)p.N_pad * 16u);
+        if constexpr (GRP) {
+            if (j == 0 && kb >= (q_cur + 1) * p.kpg) ++q_cur;  // blocks are loaded in order
+            const __amdgpu_buffer_rsrc_t rM = buf_rsrc((const uint32_t *)p.meta + (int64_t)q_cur * p.N_pad, (uint32_t)p.N_pad * 4u);
+            w.m = buf_u32(rM, n0 * 4u + 128u * j, 0);
+        }
+    };
+
+    if constexpr (GRP) {
+        // zero-point term of the K range's groups, - sum_q sc zo S_q: one more contraction,
+        // over the groups, in bf16 with both factors split into three terms (24 bits)
+        if (wfmt != LUTGEMM_WFMT_BINARY) {
+            const int qA = kbA / p.kpg + (kbA % p.kpg != 0), qB = (kbB + p.kpg - 1) / p.kpg;  // groups that start here
+            constexpr int QB = 4;  // MFMAs (pairs of groups) whose operands are loaded together
+            for (int q0 = qA; q0 < qB; q0 += 2 * QB) {
+                uint32_t mw[QB][2];
+                float sv[QB][MS];
+#pragma unroll
+                for (int u = 0; u < QB; ++u) {
+                    const int q = q0 + 2 * u + lg, qc = q < qB ? q : qB - 1;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) mw[u][j] = ((const uint32_t *)p.meta)[(int64_t)qc * p.N_pad + n0 + 32 * j];
+#pragma unroll
+                    for (int i = 0; i < MS; ++i) {
+                        const int64_t row = m0 + 32 * i + lc, r = row < p.M ? row : p.M - 1;
+                        sv[u][i] = ((const float *)p.S)[r * p.Q + qc];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < QB; ++u) {
+                    const bool live = q0 + 2 * u + lg < qB;
+                    bf16x8_t b[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const VScale s = v_scale<BITS>(wfmt, mw[u][j]);
+                        b[j] = split3_b(live ? -(s.sc * s.zo) : 0.f);
+                    }
+#pragma unroll
+                    for (int i = 0; i < MS; ++i) {
+                        const bf16x8_t a = split3_a(live ? sv[u][i] : 0.f);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[j], acc[i][j], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+
+    W w0, w1;
+    auto step = [&](int kb, const char *as, char *as_n) {
+        __builtin_amdgcn_s_waitcnt(0);  // this wavefront's loads have landed (direct LDS ones included)
+        __syncthreads();                // ... and all others'; every wavefront is done with the other buffer
+        const int kn = kb + 1 < kbB ? kb + 1 : kb;
+        load_act(kn, as_n);
+        // GRP: a block's sums are scaled into the accumulators half a chain after their last
+        // MFMA, while the next chain runs
+        floatx16_t tmp[2];
+        float scs[2] = {0.f, 0.f};
+        auto scale = [&](int c) {  // chain c = MS j + i
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[c % MS][c / MS][v] = fmaf(scs[c / MS], tmp[c & 1][v], acc[c % MS][c / MS][v]);
+        };
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            half8_t b[8];
+            W &w = j ? w1 : w0;
+            mfma_decode<BITS>(w.w, b);
+            if constexpr (GRP) scs[j] = v_scale<BITS>(wfmt, w.m).sc;
+            load_w(kn, j, w);
+            // operand reads run CP MFMAs ahead
+            half8_t a[2][CP];
+            auto read_a = [&](int h, half8_t(&d)[CP]) {  // part h % NP of chain h / NP
+                const int row = 32 * (h / NP) + lc;
+#pragma unroll
+                for (int f = 0; f < CP; ++f)
+                    d[f] = *(const half8_t *)(as + row * 256 + 16 * ((8 * lg + CP * (h % NP) + f) ^ (row & 15)));
+            };
+            read_a(0, a[0]);
+#pragma unroll
+            for (int h = 0; h < NP * MS; ++h) {
+                const int i = h / NP, c = MS * j + i;
+                if (h + 1 < NP * MS) read_a(h + 1, a[(h + 1) & 1]);
+                if constexpr (GRP) {
+                    if (h % NP == 0)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) tmp[c & 1][v] = 0.f;
+#pragma unroll
+                    for (int f = 0; f < CP; ++f)
+                        tmp[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[h & 1][f], b[CP * (h % NP) + f], tmp[c & 1], 0, 0, 0);
+                    if (h % NP == NP / 2 && c > 0) scale(c - 1);
+                } else {
+#pragma unroll
+                    for (int f = 0; f < CP; ++f)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[h & 1][f], b[CP * (h % NP) + f], acc[i][j], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (GRP) scale(2 * MS - 1);
+    };
+
+    load_act(kbA, A0);
+    load_w(kbA, 0, w0);
+    load_w(kbA, 1, w1);
+    int kb = kbA;
+    for (; kb + 1 < kbB; kb += 2) {
+        step(kb, A0, A1);
+        step(kb + 1, A1, A0);
+    }
+    if (kb < kbB) step(kb, A0, A1);
+
+    // Epilogue.  The lane holds column lane % 32, rows 8 (v / 4) + 4 (lane / 32) + v % 4 of
+    // each 32 x 32 block; 16 rows of the wavefront's 64 columns at a time go through LDS so
+    // that a row leaves in one store of 64 consecutive columns and the row's operands are
+    // uniform.
+    __builtin_amdgcn_s_waitcnt(0);  // (the last step's prefetch has landed)
+    __syncthreads();                // the activation buffers are free
+    float *ew = (float *)E + wave * (16 * 64);
+    const int64_t n = (int64_t)tl.nt * NTILE + wave * 64 + lane;  // column of this lane from here on
+    float sc = 1.f, nsz = 0.f;
+    if constexpr (!GRP) {
+        const VScale s = p.per_tensor ? v_scale_f<BITS>(wfmt, ((const float *)p.meta)[0], ((const float *)p.meta)[1])
+                                      : v_scale<BITS>(wfmt, ((const uint32_t *)p.meta)[n]);
+        sc = s.sc;
+        nsz = -(s.sc * s.zo);
+    }
+    const bool zero_term = !GRP && wfmt != LUTGEMM_WFMT_BINARY && tl.split == 0;  // whole K: the first split adds it
+    const int64_t m_alloc = (int64_t)m_tiles * ROWS;
+#pragma unroll
+    for (int i = 0; i < MS; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 8; ++v) ew[(8 * (v >> 2) + 4 * lg + (v & 3)) * 64 + 32 * j + lc] = acc[i][j][8 * h + v];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+            const int64_t mr = m0 + 32 * i + 16 * h;
+            const int rows = (int)(p.M - mr < 16 ? (p.M - mr < 0 ? 0 : p.M - mr) : 16);
+#pragma unroll 1
+            for (int r = 0; r < rows; ++r) {
+                float y = ew[r * 64 + lane];
+                const int64_t m = mr + r;
+                if constexpr (!GRP) {
+                    y *= sc;
+                    if (zero_term) y = fmaf(nsz, ((const float *)p.S)[m], y);
+                }
+                if (p.splits > 1) {
+                    p.part[((int64_t)tl.split * m_alloc + m) * p.N_pad + n] = y;
+                } else if (n < p.N) {
+                    const Epi ep = load_epi<false>(p, wfmt, m, n, false);
+                    store_out<false>(p, wfmt, m, n, y, 0, ep);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+        }
+}
+
+// ---------------------------------------------------------------- launch
+
+template <int BITS, int MS>
+static void launch_mfma_ms(const LutParams &p, const Layout &L, const LutPlan &plan, hipStream_t s) {
+    const dim3 grid((unsigned)(plan.n_tiles * plan.m_tiles * plan.splits));
+    const uint32_t nt = (uint32_t)plan.n_tiles, mt = (uint32_t)plan.m_tiles;
+    if (L.Q > 1)
+        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, true, MS>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+    else
+        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, false, MS>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+}
+
+int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, float *S, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t waves = (L.K + 2047) / 2048;
+    const int threads = (int)(waves < 4 ? 64 * waves : 256);
+    const size_t shm = S ? (size_t)L.KB * 4 : 0;
+    const int Q = (int)L.Q, kpg = (int)(L.G / KBLK);
+    if (p.act) hipLaunchKernelGGL(prep_kernel<false>, dim3((unsigned)p.M), dim3(threads), shm, s, p.act, (uint4 *)dst, S, L.K, Q, kpg);
+    else hipLaunchKernelGGL(prep_kernel<true>, dim3((unsigned)p.M), dim3(threads), shm, s, p.T, (uint4 *)dst, S, L.K, Q, kpg);
+    return (int)hipGetLastError();
+}
+
+int launch_mfma(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    switch (L.bits * 8 + plan.mt / 32) {
+    case 8 + 1: launch_mfma_ms<1, 1>(p, L, plan, s); break;
+    case 8 + 2: launch_mfma_ms<1, 2>(p, L, plan, s); break;
+    case 8 + 4: launch_mfma_ms<1, 4>(p, L, plan, s); break;
+    case 16 + 1: launch_mfma_ms<2, 1>(p, L, plan, s); break;
+    case 16 + 2: launch_mfma_ms<2, 2>(p, L, plan, s); break;
+    case 16 + 4: launch_mfma_ms<2, 4>(p, L, plan, s); break;
+    case 32 + 1: launch_mfma_ms<4, 1>(p, L, plan, s); break;
+    case 32 + 2: launch_mfma_ms<4, 2>(p, L, plan, s); break;
+    case 32 + 4: launch_mfma_ms<4, 4>(p, L, plan, s); break;
+    default: return (int)hipErrorInvalidValue;
+    }
+    return (int)hipGetLastError();
+}
+
+}  // namespace lutgemm

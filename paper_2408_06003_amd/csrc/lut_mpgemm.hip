@@ -79,7 +79,7 @@ int launch_lut(const LutParams &p, const Layout &L, const LutPlan &plan, void *s
 // Sums the K-split partials of the LUT kernel (after it, on the same stream).
 int launch_finalize(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream) {
     hipStream_t s = (hipStream_t)stream;
-    const int64_t m_alloc = plan.kind == 1 ? plan.m_tiles * plan.mt : p.M;
+    const int64_t m_alloc = plan.kind == 1 || plan.kind == 4 ? plan.m_tiles * plan.mt : p.M;
     const int pt = L.per_tensor ? 1 : 0;
     // single tokens: 64-lane workgroups spread the few columns over many CUs; several
     // tokens: 256 lanes, a quarter of the workgroups

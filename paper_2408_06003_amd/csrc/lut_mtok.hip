@@ -73,29 +73,6 @@ __device__ __forceinline__ uint32_t neg16x2(uint32_t x) {
     return x ^ 0x80008000u;  // FP16: flip both sign bits (exact)
 }
 
-// Raw buffer resource over `bytes` bytes at `base` (stride 0; a load at or past the
-// extent returns 0).  Loads through it take a 32-bit lane offset and a
-// workgroup-uniform scalar offset, so they need no 64-bit address arithmetic.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ uint32_t buf_u32(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    return __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0);
-}
-__device__ __forceinline__ uint32_t buf_u16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    return __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
-}
-__device__ __forceinline__ uint2 buf_u64(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
-    return make_uint2(v.x, v.y);
-}
-__device__ __forceinline__ uint4 buf_u128(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // (x >> 8 j) & 0xF0 for a compile-time byte j (after unrolling) in one SDWA
 // instruction: the high nibble of byte j of x, times 16, i.e. the byte offset of
 // that Eq. 6 index's row in a token-interleaved table.  (The compiler emits a

@@ -149,25 +149,32 @@ inline TableLayout make_table_layout(const Layout &L, int64_t M) {
 // Launch plan of the LUT mpGEMM for (problem, M).
 struct LutPlan {
     int kind;        // 0: single-token whole-K GEMV, 1: multi-token kernel, 2: single-token split-K GEMV,
-                     // 3: ternary 3-in-5 kernel (whole K, any M)
+                     // 3: ternary 3-in-5 kernel (whole K, any M), 4: matrix-core kernel
     int gemv_cfg;    // single-token kernel: lane decomposition (see lut_gemv.hip)
     int kbs;         // 128-blocks of K per split
     int pre;         // split-K GEMV: weight words per lane requested before the tables are waited for
     bool inkernel;   // split-K GEMV: the K split is completed in the kernel (else by the finalize kernel)
     bool exact;      // split-K GEMV: ... by one 64-bit atomic per output on exact integer partials
     int splits;      // K splits (1 = no workspace)
-    int mt;          // tokens per workgroup (multi-token kernel)
+    int mt;          // tokens per workgroup (multi-token and matrix-core kernels)
     int64_t m_tiles; // token tiles
     int64_t n_tiles; // column tiles
     int order;       // multi-token kernel: workgroup order (0: columns fastest; 1: tokens fastest
                      // per XCD; g >= 2: per XCD, bands of g token tiles, tokens fastest in a band)
     size_t ws_bytes;
     size_t part_off;  // byte offset of the split partial sums in the workspace (counters at 0)
+    size_t prep_off, prep_s_off;  // matrix-core kernel: prepared activations and their group sums
 };
 
 // fused: the plan of lutgemm_mpgemm_fused (the multi-token kernel that builds its tables
 // from the activations keeps a K range within MTOK_FUSED_SMAX blocks for zero-point formats)
 LutPlan plan_lut(const Layout &L, int64_t M, bool fused = false);
+
+// The matrix-core plan of (problem, M), kind 4, or kind -1 where the lookup kernels are planned.
+LutPlan plan_mfma(const Layout &L, int64_t M);
+
+// Smallest workspace lutgemm_mpgemm accepts for a valid problem: that of the lookup kernels.
+size_t min_workspace(const lutgemm_problem_t *problem, int64_t M);
 
 // Current value of planner override `key` (LUTGEMM_TUNE_*, see lutgemm_set_tuning).
 int tuning(int key);
@@ -256,6 +263,10 @@ int launch_finalize(const LutParams &p, const Layout &L, const LutPlan &plan, vo
 int launch_mtok(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
 // The multi-token kernel building its tables from the FP16 activations (p.act).
 int launch_mtok_fused(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
+// Matrix-core path: the activations in operand order, from p.act or (NULL) the half tables
+// p.T, with their group sums if S != NULL; then the product (p.act = the prepared ones).
+int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, float *S, void *stream);
+int launch_mfma(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
 int launch_tri(const LutParams &p, const Layout &L, bool fused, void *stream);
 int launch_dequant(const DequantParams &p, const Layout &L, const DequantPlan &plan, void *stream);
 

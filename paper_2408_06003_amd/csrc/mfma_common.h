@@ -1,0 +1,174 @@
+// Device helpers of the matrix-core kernels: operand layout, weight decode from the packed
+// bit-planes, and the scale / zero-point constants of the decoded values.
+#pragma once
+
+#include "lut_common.h"
+
+namespace lutgemm {
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float floatx16_t __attribute__((ext_vector_type(16)));
+
+// Chunk t (8 halves) of a 32-activation word in the MFMA order: activations 4 t + e (low
+// halves) and 4 t + e + 16 (high halves), e = 0..3.  x: the word's 32 halves in order.
+__device__ __forceinline__ uint4 mfma_chunk(const uint4 (&x)[4], int t) {
+    const uint4 lo4 = x[t >> 1], hi4 = x[2 + (t >> 1)];
+    const uint32_t lx = (t & 1) ? lo4.z : lo4.x, ly = (t & 1) ? lo4.w : lo4.y;
+    const uint32_t hx = (t & 1) ? hi4.z : hi4.x, hy = (t & 1) ? hi4.w : hi4.y;
+    return make_uint4(__builtin_amdgcn_perm(hx, lx, 0x05040100u), __builtin_amdgcn_perm(hx, lx, 0x07060302u),
+                      __builtin_amdgcn_perm(hy, ly, 0x05040100u), __builtin_amdgcn_perm(hy, ly, 0x07060302u));
+}
+
+// The four activations behind a half table of FP16 entries (least squares), as FP16.
+__device__ __forceinline__ uint2 table_acts(uint4 e) {
+    const float t0 = h2f(e.x & 0xFFFFu), t1 = h2f(e.x >> 16), t2 = h2f(e.y & 0xFFFFu), t3 = h2f(e.y >> 16);
+    const float t4 = h2f(e.z & 0xFFFFu), t5 = h2f(e.z >> 16), t6 = h2f(e.w & 0xFFFFu), t7 = h2f(e.w >> 16);
+    // entry i: -x0, +x1 if i & 4, +x2 if i & 2, +x3 if i & 1 (else minus)
+    const float s0 = t0 + t1, s1 = t2 + t3, s2 = t4 + t5, s3 = t6 + t7;
+    const float u0 = s0 + s1, u1 = s2 + s3;
+    const float x3 = ((t1 - t0) + (t3 - t2)) + ((t5 - t4) + (t7 - t6));
+    const float x2 = (s1 - s0) + (s3 - s2);
+    const float x1 = u1 - u0, x0 = -(u0 + u1);
+    auto pack = [](float a, float b) {
+        return (uint32_t)__half_as_ushort(__float2half_rn(a * 0.125f)) | ((uint32_t)__half_as_ushort(__float2half_rn(b * 0.125f)) << 16);
+    };
+    return make_uint2(pack(x0, x1), pack(x2, x3));
+}
+
+// Low 3 bits of every 4-bit index inverted where its bit 3 is set: undoes the offline
+// negation of Eq. 6 for 8 indices at once (8 - 1 = 7 per set sign bit).
+__device__ __forceinline__ uint32_t undo_neg(uint32_t w) {
+    const uint32_t m = w & 0x88888888u;
+    return w ^ (m - (m >> 3));
+}
+
+// (a & mask) | (b & ~mask)
+__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
+
+// x shifted so that bit `from` lands at bit `to` (compile-time after unrolling).
+__device__ __forceinline__ uint32_t shift_to(uint32_t x, int from, int to) {
+    return to >= from ? x << (to - from) : x >> (from - to);
+}
+
+// The 8 MFMA operand fragments (steps f = 4 j + t) of a lane from its two words per plane.
+template <int BITS>
+__device__ __forceinline__ void mfma_decode(const uint2 (&w)[BITS], half8_t (&b)[8]) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        uint32_t y[BITS];
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) y[t] = undo_neg(j ? w[t].y : w[t].x);
+        if constexpr (BITS == 1) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                u32x4 r;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int s = 4 * t + 3 - e;  // bit of activation 4 t + e
+                    r[e] = (~shift_to(y[0], s, 15) & 0x80008000u) | 0x3C003C00u;
+                }
+                b[4 * j + t] = __builtin_bit_cast(half8_t, r);
+            }
+        } else if constexpr (BITS == 2) {
+            // fields (bit 1, bit 0) of even bit positions in u0, of odd ones in u1
+            const uint32_t u0 = bfi(0x55555555u, y[0], y[1] << 1), u1 = bfi(0x55555555u, y[0] >> 1, y[1]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                u32x4 r;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int s = 4 * t + 3 - e;
+                    r[e] = (shift_to((s & 1) ? u1 : u0, s & ~1, 8) & 0x03000300u) | 0x3C003C00u;
+                }
+                b[4 * j + t] = __builtin_bit_cast(half8_t, r);
+            }
+        } else {
+            static_assert(BITS == 4, "1, 2 or 4 bit-planes");
+            const uint32_t a0 = bfi(0x55555555u, y[0], y[1] << 1), a1 = bfi(0x55555555u, y[0] >> 1, y[1]);
+            const uint32_t c0 = bfi(0x55555555u, y[2], y[3] << 1), c1 = bfi(0x55555555u, y[2] >> 1, y[3]);
+            // 4-bit fields of the bit positions = 0, 1, 2, 3 modulo 4
+            const uint32_t n[4] = {bfi(0x33333333u, a0, c0 << 2), bfi(0x33333333u, a1, c1 << 2),
+                                   bfi(0x33333333u, a0 >> 2, c0), bfi(0x33333333u, a1 >> 2, c1)};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                u32x4 r;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[e] = (shift_to(n[3 - e], 4 * t, 6) & 0x03C003C0u) | 0x3C003C00u;
+                b[4 * j + t] = __builtin_bit_cast(half8_t, r);
+            }
+        }
+    }
+}
+
+// w = sc (v - zo) for the decoded FP16 value v.
+struct VScale {
+    float sc, zo;
+};
+template <int BITS>
+__device__ __forceinline__ VScale v_scale_f(int wfmt, float s, float z) {
+    if (wfmt == LUTGEMM_WFMT_BINARY) return {s, 0.f};
+    if (wfmt == LUTGEMM_WFMT_TERNARY) z = 1.f;  // q = w + 1
+    if constexpr (BITS == 1) return {0.5f * s, 2.f * z - 1.f};
+    constexpr float C = (float)(1 << BITS);
+    return {C * s, fmaf(z, 1.f / C, 1.f)};
+}
+template <int BITS>
+__device__ __forceinline__ VScale v_scale(int wfmt, uint32_t meta) {
+    return v_scale_f<BITS>(wfmt, h2f(meta & 0xFFFFu), h2f(meta >> 16));
+}
+
+// x as three bf16 terms hi + mid + lo (8 significant bits each); the operand slots of the
+// 8 products that matter: sum_i a_i b_i = x y to about 2^-24.
+struct Split3 {
+    uint32_t h, m, l;  // bf16 bits
+};
+__device__ __forceinline__ Split3 split3(float x) {
+    const uint32_t hb = __float_as_uint(x) & 0xFFFF0000u;
+    const float r = x - __uint_as_float(hb);
+    const uint32_t mb = __float_as_uint(r) & 0xFFFF0000u;
+    const float r2 = r - __uint_as_float(mb);
+    return {hb >> 16, mb >> 16, __float_as_uint(r2) >> 16};
+}
+__device__ __forceinline__ bf16x8_t split3_a(float x) {
+    const Split3 s = split3(x);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(bf16x8_t, (u32x4){s.h | (s.h << 16), s.m | (s.h << 16), s.l | (s.m << 16), s.m | (s.l << 16)});
+}
+__device__ __forceinline__ bf16x8_t split3_b(float x) {
+    const Split3 s = split3(x);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(bf16x8_t, (u32x4){s.h | (s.m << 16), s.h | (s.l << 16), s.h | (s.m << 16), s.l | (s.m << 16)});
+}
+
+// Quantization group of 128-block kb (workgroup-uniform).
+__device__ __forceinline__ int kb_group(const LutParams &p, int kb) {
+    return __builtin_amdgcn_readfirstlane((int)(((float)kb + 0.5f) * p.inv_kpg));
+}
+
+struct MTile {
+    uint32_t nt, mt;
+    int split;
+};
+// Tile of a workgroup.  Workgroups are dealt round robin to the 8 XCDs; each XCD gets its
+// own contiguous share of the tile space, walked in bands of `order` token tiles (tokens
+// fastest), so that what one XCD runs at a time shares activation rows and weight columns
+// in its L2.  Splits of K vary slowest.
+__device__ __forceinline__ MTile mfma_tile(uint32_t b, uint32_t n_tiles, uint32_t m_tiles, int order) {
+    const uint32_t per_split = n_tiles * m_tiles, total = gridDim.x;
+    const uint32_t q = total >> 3, r = total & 7, x = b & 7, i = b >> 3;
+    b = x * q + (x < r ? x : r) + i;
+    MTile t;
+    t.split = (int)(b / per_split);
+    const uint32_t w = b - (uint32_t)t.split * per_split;
+    const uint32_t o = (uint32_t)order;
+    const uint32_t band = w / (o * n_tiles), first = band * o;
+    const uint32_t rows = (m_tiles - first) < o ? (m_tiles - first) : o;
+    const uint32_t v = w - band * o * n_tiles;
+    t.mt = first + v % rows;
+    t.nt = v / rows;
+    return t;
+}
+
+}  // namespace lutgemm

@@ -36,7 +36,8 @@ extern "C" lutgemm_status_t lutgemm_mpgemm_noalloc(const lutgemm_problem_t *prob
                                                    int32_t out_dtype, int32_t accumulate, void *stream) {
     lutgemm_status_t st = lutgemm_validate(problem, M);
     if (st != LUTGEMM_SUCCESS) return st;
-    const size_t need = lutgemm_workspace_size(problem, M);
+    // (calls whose matrix-core plan needs more than the array run the lookup kernels)
+    const size_t need = lutgemm::min_workspace(problem, M);
     if (need > LUTGEMM_NOALLOC_SCRATCH_BYTES) {
         char msg[160];
         std::snprintf(msg, sizeof(msg), "lutgemm_mpgemm_noalloc: needs %zu bytes of scratch, the static array holds %zu",
@@ -45,7 +46,7 @@ extern "C" lutgemm_status_t lutgemm_mpgemm_noalloc(const lutgemm_problem_t *prob
         return LUTGEMM_ERROR_NOT_SUPPORTED;
     }
     void *ws = nullptr;
-    if (need > 0) {
+    if (lutgemm_workspace_size(problem, M) > 0) {
         int dev = -1;
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return lutgemm::hip_error(e);

@@ -281,3 +281,25 @@ def test_tuning_overrides():
             assert L.workspace_size(L.problem(8192, 28672, 1, L.WFMT_BINARY, 8192), 1) > ws
     finally:
         L.set_tuning("GEMV_KIND", old)
+
+
+def test_matrix_core_plan():
+    """From 16 FP16 tokens on the workspace covers the matrix-core path (prepared activations
+    of whole token tiles); an override of the lookup kernel's plan, or the key itself, takes
+    the lookup kernels' size back."""
+    p = L.problem(4096, 4096, 2, L.WFMT_UINT, 128)
+    with tuning(MFMA=0):
+        assert L.workspace_size(p, 4096) == 0
+        small = L.workspace_size(p, 15)
+    assert L.workspace_size(p, 4096) >= L.WORKSPACE_ZERO_BYTES + 4096 * 4096 * 2
+    assert L.workspace_size(p, 15) == small
+    with tuning(MT_ORDER=1):
+        assert L.workspace_size(p, 4096) == 0
+    for M in (16, 100, 4096):
+        assert L.fused_workspace_size(p, M) >= L.workspace_size(p, M)
+    i8 = L.problem(4096, 4096, 2, L.WFMT_TERNARY, 0, L.ACT_INT8, True)
+    q8 = L.problem(4096, 4096, 2, L.WFMT_UINT, 128, L.ACT_FP16_LUT8)
+    for other in (i8, q8):
+        with tuning(MFMA=0):
+            ws = L.workspace_size(other, 4096)
+        assert L.workspace_size(other, 4096) == ws

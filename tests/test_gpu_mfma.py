@@ -1,0 +1,131 @@
+"""Several tokens on the matrix cores (lut_mfma.hip): every tile size and K split where its
+bookkeeping can go wrong, every weight format and scale layout, against the CPU oracle.
+
+Tolerances.  Fused calls (FP16 activations): codes and activations are exact in FP16 and
+products in FP32, so FP32 outputs differ from the exact product by FP32 summation only:
+relative error at most about sqrt(K) 2^-24 of the terms' magnitude, and the zero-point term
+(sums of offset codes, up to 31 times the result for 4 bits) scales that; 1e-5 bounds it at
+these K.  Table-fed calls: the FP bar of the lookup kernels (the activations come from FP16
+table entries).
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from helpers import GpuProblem, assert_fp_close, fp_errors
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2408_06003_amd as L  # noqa: E402
+
+CASES = [
+    # (weight format, bits, group, FP32 per-tensor scale, M, K, N)
+    (W.WFMT_UINT, 4, 128, False, 70, 1152, 300),     # 9 blocks: an odd last step
+    (W.WFMT_UINT, 2, 512, False, 129, 2048, 257),    # groups of 4 blocks, split mid-group
+    (W.WFMT_UINT, 1, 128, False, 33, 128, 1),        # one block, one column
+    (W.WFMT_UINT, 1, 0, False, 17, 640, 255),        # one FP16 scale and zero per tensor
+    (W.WFMT_UINT, 4, 1280, False, 5, 1280, 513),     # per channel
+    (W.WFMT_BINARY, 1, 256, False, 40, 1536, 300),   # group scales, no zero point
+    (W.WFMT_BINARY, 1, 0, True, 128, 384, 256),      # one FP32 scale, whole tiles
+    (W.WFMT_TERNARY, 2, 128, False, 65, 1024, 300),  # grouped, z = 1
+    (W.WFMT_TERNARY, 2, 0, True, 3, 2944, 100),
+]
+
+
+@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("wfmt,bits,G,fp32,M,K,N", CASES)
+def test_formats_tiles_splits(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
+    tune(MFMA=1, MFMA_TILE=tile, MFMA_SPLITS=splits)
+    what = f"wfmt={wfmt} b={bits} G={G} M={M} K={K} N={N} tile={tile} splits={splits}"
+    print(f"\n[case] {what}", flush=True)
+    inp = W.make_custom(wfmt, bits, G, W.ACT_FP16, M=M, K=K, N=N, seed=M + K + N, scale_fp32=fp32)
+    gp = GpuProblem(inp)
+    ref = oracle.reference_output(inp)
+    y = gp.fused(out_dtype=torch.float32)
+    fro, _ = fp_errors(y.cpu().numpy(), ref)
+    assert fro <= 1e-5, f"{what}: fused relative error {fro:.3e}"
+    assert torch.equal(gp.fused(out_dtype=torch.float32), y), f"{what}: two runs differ bitwise"
+    assert torch.equal(gp.fused(out_dtype=torch.float16), y.half()), f"{what}: FP16 output is not the rounded FP32 one"
+    assert_fp_close(gp.lut(out_dtype=torch.float32).cpu().numpy(), ref, what + " table-fed")
+
+
+@pytest.mark.parametrize("splits", [1, 4])
+def test_tokens_and_accumulate(splits, tune):
+    """Tokens of very different magnitude (FP16 subnormals, a zero token, large ones) each to
+    their own accuracy, and O += A W^T with FP32 and FP16 outputs."""
+    tune(MFMA=1, MFMA_SPLITS=splits)
+    print(f"\n[case] magnitudes and accumulate, splits={splits}", flush=True)
+    inp = W.make_custom(W.WFMT_UINT, 2, 128, W.ACT_FP16, M=20, K=1024, N=300, seed=77)
+    a = inp.act.astype(np.float32)
+    a[3] *= 1e-5
+    a[4] = 0.0
+    a[5] *= 1e4
+    inp.act = a.astype(np.float16)
+    gp = GpuProblem(inp)
+    ref = oracle.reference_output(inp)
+    yf, yt = gp.fused(out_dtype=torch.float32), gp.lut(out_dtype=torch.float32)
+    for m in range(20):
+        if m == 4:
+            assert not yf[m].any() and not yt[m].any()
+            continue
+        assert fp_errors(yf[m].cpu().numpy(), ref[m])[0] <= 1e-5, m
+        assert_fp_close(yt[m].cpu().numpy(), ref[m], f"table-fed token {m}")
+    for run, y in ((gp.fused, yf), (gp.lut, yt)):
+        base = torch.randn(20, 300, device="cuda")
+        acc = base.clone()
+        run(out=acc, accumulate=True)
+        assert torch.equal(acc, base + y)
+        base16 = base.half()
+        acc16 = base16.clone()
+        run(out=acc16, accumulate=True)
+        assert torch.equal(acc16, (base16.float() + y).half())
+
+
+def test_small_workspace_runs_the_lookup_kernels():
+    """A workspace that holds only what the lookup kernels need is still accepted (here
+    none at all: no K split), and gives the lookup kernels' result."""
+    print("\n[case] table-fed without a workspace", flush=True)
+    inp = W.make_custom(W.WFMT_UINT, 2, 128, W.ACT_FP16, M=300, K=256, N=16384, seed=78)
+    gp = GpuProblem(inp)
+    tables = gp.g.tables(300)
+    L.precompute(gp.p, 300, gp.act, tables)
+    out = torch.empty((300, 16384), dtype=torch.float32, device="cuda")
+    assert L.workspace_size(gp.p, 300) > 0
+    L.set_tuning("MFMA", 0)
+    try:
+        assert L.workspace_size(gp.p, 300) == 0
+        ref = gp.lut(out_dtype=torch.float32)
+    finally:
+        L.set_tuning("MFMA", -1)
+    L.mpgemm(gp.p, 300, tables, gp.g.packed, out, L.OUT_FP32)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+
+
+def test_graph_replay(tune):
+    """Prepare, multiply and finalize captured in one graph, replayed with eager work between."""
+    print("\n[case] graph replay of a split matrix-core call", flush=True)
+    tune(MFMA=1, MFMA_SPLITS=3)
+    inp = W.make_custom(W.WFMT_UINT, 4, 128, W.ACT_FP16, M=40, K=1024, N=300, seed=79)
+    gp = GpuProblem(inp)
+    out = torch.zeros((40, 300), dtype=torch.float32, device="cuda")
+    ref = gp.fused(out_dtype=torch.float32)
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        for _ in range(3):
+            gp.g.fused(gp.act, out=out)
+    for _ in range(3):
+        out.zero_()
+        gp.lut(out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
