@@ -569,7 +569,7 @@ __device__ __forceinline__ void split_complete(const LutParams &p, int wfmt, int
 // entries (every block shares s', so the output is s' 2^-FIX_SHIFT times the total
 // minus the zero-point term: sx, sy); otherwise the FP32 partial sum in fixed point,
 // v = rint(partial 2^-E) with the column's exponent E (|v| < 2^BND_BITS, see
-// pack_bound_kernel), the output 2^E times the total.  The zeroed word of (m, n)
+// bound_exponent in pack.hip), the output 2^E times the total.  The zeroed word of (m, n)
 // accumulates c 2^57 + V (c arrivals, V the signed sum so far, |V| < 2^56): each split
 // adds 2^57 + v with one agent-coherent atomic and gets the previous word back, and
 // the split that sees c = splits - 1 holds the exact total, which integer addition

@@ -13,60 +13,140 @@
 
 namespace lutgemm {
 
-// 4-bit stored index of one plane over 4 codes (first code = MSB), Eq. 6.
-__device__ __forceinline__ uint32_t plane_index(uint32_t q0, uint32_t q1, uint32_t q2, uint32_t q3,
-                                                int t) {
-    uint32_t pat = (((q0 >> t) & 1u) << 3) | (((q1 >> t) & 1u) << 2) | (((q2 >> t) & 1u) << 1) |
-                   ((q3 >> t) & 1u);
-    uint32_t sign = pat >> 3;
-    uint32_t low = sign ? (~pat & 7u) : (pat & 7u);
-    return (sign << 3) | low;
+// 4 codes (one byte each) as read by the planes: UINT and BINARY codes as they are (a plane
+// takes bit t only, so they count modulo 2^b); TERNARY w clamped to {-1, 0, 1} as q = w + 1,
+// i.e. bit 0 where the byte is zero and bit 1 where it is positive.
+__device__ __forceinline__ uint32_t plane_codes(uint32_t w, bool ternary) {
+    if (!ternary) return w;
+    const uint32_t nonzero = (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
+    const uint32_t zero = nonzero ^ 0x80808080u, pos = nonzero & ~w;
+    return (zero >> 7) | (pos >> 6);
 }
 
-// Code q of byte e of a 32-bit load of 4 consecutive codes.
-__device__ __forceinline__ uint32_t code_of(const PackParams &p, uint32_t word, int e) {
-    uint32_t c = (word >> (8 * e)) & 0xFFu;
-    if (p.wfmt == LUTGEMM_WFMT_TERNARY) {
-        int v = (int)(int8_t)c;
-        v = v < -1 ? -1 : (v > 1 ? 1 : v);
-        return (uint32_t)(v + 1);
+// The planes of one 128-block of a column from its 128 code bytes.  The pattern of plane t
+// over 4 codes (first code = MSB) is a dot product of their bits with 8, 4, 2, 1
+// (v_dot4_u32_u8); two groups share a byte through weights 16 times as large, and the factor
+// 2^t of the unshifted bits leaves with the byte's final shift.  Eq. 6 on whole words: the
+// low 3 bits of every index whose MSB is set are inverted (8 - 1 = 7 per set MSB).
+template <int BITS>
+__device__ __forceinline__ void pack_block(const uint4 (&c)[8], bool ternary, uint4 (&out)[BITS]) {
+    uint32_t word[BITS][4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t g[8] = {c[2 * d].x, c[2 * d].y, c[2 * d].z, c[2 * d].w, c[2 * d + 1].x, c[2 * d + 1].y, c[2 * d + 1].z, c[2 * d + 1].w};
+        uint32_t q[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = plane_codes(g[i], ternary);
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) {
+            const uint32_t m = 0x01010101u << t;
+            uint32_t w = 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t b = __builtin_amdgcn_udot4(q[2 * i + 1] & m, 0x10204080u,
+                                                          __builtin_amdgcn_udot4(q[2 * i] & m, 0x01020408u, 0u, false), false);
+                w |= (8 * i >= t ? b << (8 * i - t) : b >> (t - 8 * i));
+            }
+            const uint32_t msb = w & 0x88888888u;
+            word[t][d] = w ^ (msb - (msb >> 3));
+        }
     }
-    return c & ((1u << p.bits) - 1u);
+#pragma unroll
+    for (int t = 0; t < BITS; ++t) out[t] = make_uint4(word[t][0], word[t][1], word[t][2], word[t][3]);
 }
 
-// One thread per (column n, 128-block kb), kb fastest so that a wavefront reads
-// consecutive 128-byte code segments of one row.
-__global__ __launch_bounds__(256) void pack_planes_kernel(PackParams p) {
-    const int64_t total = p.N_pad * p.KB;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t kb = idx % p.KB;
-        const int64_t n = idx / p.KB;
-        uint32_t w[4][4];
+// Fixed-point exponent E of column n for the exact K-split completion of FP partial
+// sums (split_complete_exact).  With the token scaled to |x| < 1 by the precompute, a
+// table entry (a signed sum of 4 activations) is below 4 in magnitude, stored as at
+// most 4 2^FIX_SHIFT, so one 128-block of bit-plane t adds at most |s'| 2^t 128 to a
+// partial sum and the zero-point term of a group is at most |s' z'| G (|S| <= G).
+// Their sum over the column's groups, B (with 1/16 added for the FP32 rounding of the
+// partial sums), bounds every split's partial sum and their total; E is the smallest
+// integer with B < 2^(BND_BITS + E).  (The fused split kernel, whose tables hold the
+// unscaled FP16 activations, |x| <= 65504 < 2^16, uses E + 16.)  E = 0 for padding
+// columns and all-zero scales; B is not finite only for non-finite scales, whose
+// outputs are unspecified on this path.
+struct BoundConsts {
+    float cs, cz, c0;  // Eq. 2 of the format
+};
+__device__ __forceinline__ double bound_term(const PackParams &p, const BoundConsts &k, float s, float z) {
+    const double kpg = (double)(p.G / KBLK), planes = (double)((1 << p.bits) - 1), G = (double)p.G;
+    const double sp = (double)k.cs * (double)s, zp = (double)k.cz * (double)z + (double)k.c0;
+    return kpg * fabs(sp) * 128.0 * planes + fabs(sp * zp) * G;
+}
+__device__ __forceinline__ int bound_exponent(double B) {
+    B *= 1.0625;
+    return B > 0.0 && B <= 1e300 ? ilogb(B) + 1 - BND_BITS : 0;
+}
+
+// Planes, metadata and exponents in one launch.  Workgroups below `plane_wgs`: a wavefront
+// packs one 128-block of 64 columns, one column per lane, the 4 wavefronts 4 consecutive
+// blocks.  A lane reads its 128 code bytes with eight 16-byte loads (whole cache lines, all
+// of them in flight) and stores one word per plane, 1 KiB contiguous per wavefront; the work
+// is then the read of the codes: 4096 x 12288 INT4 21.6 us, 3.6 TB/s.  (One thread per column
+// and block, block fastest, and two more launches for the metadata took 244 us: its stores
+// were 16 bytes each, b N_pad 16 bytes apart.)
+// Workgroups from `plane_wgs`: one column per lane, its (s, z) pairs [Q][N_pad] (per tensor:
+// two FP32 values) and its exponent, groups in order, 8 in flight.
+template <int BITS>
+__global__ __launch_bounds__(256) void pack_kernel(PackParams p, uint32_t plane_wgs, BoundConsts k) {
+    const int lane = threadIdx.x & 63;
+    if (blockIdx.x < plane_wgs) {
+        const int64_t task = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+        const int64_t kb = task % p.KB, n = task / p.KB * 64 + lane;
+        if (n >= p.N_pad) return;
+        uint4 out[BITS];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) w[t][d] = 0u;
+        for (int t = 0; t < BITS; ++t) out[t] = make_uint4(0u, 0u, 0u, 0u);
         if (n < p.N) {
-            const int64_t base = n * p.K + kb * KBLK;
-            const uint32_t *row = (const uint32_t *)((const uint8_t *)p.codes + base);
+            const uint4 *row = (const uint4 *)((const uint8_t *)p.codes + n * p.K + kb * KBLK);
+            uint4 c[8];
 #pragma unroll
-            for (int g = 0; g < GPB; ++g) {
-                const uint32_t word = row[g];
-                const uint32_t q0 = code_of(p, word, 0), q1 = code_of(p, word, 1);
-                const uint32_t q2 = code_of(p, word, 2), q3 = code_of(p, word, 3);
+            for (int i = 0; i < 8; ++i) c[i] = row[i];
+            pack_block<BITS>(c, p.wfmt == LUTGEMM_WFMT_TERNARY, out);
+        }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    if (t < p.bits) w[t][g >> 3] |= plane_index(q0, q1, q2, q3, t) << (4 * (g & 7));
-                }
+        for (int t = 0; t < BITS; ++t) p.planes[(kb * BITS + t) * p.N_pad + n] = out[t];
+        return;
+    }
+    const int64_t n = (int64_t)(blockIdx.x - plane_wgs) * 256 + threadIdx.x;
+    if (n >= p.N_pad) return;
+    const bool zeros = p.wfmt == LUTGEMM_WFMT_UINT;
+    double B = 0.0;
+    if (p.per_tensor) {
+        float s, z = 0.f;
+        if (p.scale_fp32) {
+            s = ((const float *)p.scales)[0];
+        } else {
+            s = __half2float(((const __half *)p.scales)[0]);
+            if (zeros) z = __half2float(((const __half *)p.zeros)[0]);
+        }
+        if (n == 0) {
+            ((float *)p.meta)[0] = s;
+            ((float *)p.meta)[1] = z;
+        }
+        if (n < p.N) B = bound_term(p, k, s, z);
+    } else {
+        for (int64_t q0 = 0; q0 < p.Q; q0 += 8) {
+            uint32_t w[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int64_t q = q0 + i < p.Q ? q0 + i : p.Q - 1;
+                const int64_t at = (n < p.N ? n : p.N - 1) * p.Q + q;
+                w[i] = ((const uint16_t *)p.scales)[at];
+                if (zeros) w[i] |= (uint32_t)((const uint16_t *)p.zeros)[at] << 16;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (q0 + i >= p.Q) break;
+                ((uint32_t *)p.meta)[(q0 + i) * p.N_pad + n] = n < p.N ? w[i] : 0u;
+                if (n < p.N)
+                    B += bound_term(p, k, __half2float(__ushort_as_half((unsigned short)(w[i] & 0xFFFFu))),
+                                    __half2float(__ushort_as_half((unsigned short)(w[i] >> 16))));
             }
         }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (t < p.bits)
-                p.planes[(kb * p.bits + t) * p.N_pad + n] = make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
-        }
     }
+    p.bnd[n] = n < p.N ? bound_exponent(B) : 0;
 }
 
 // Ternary 3-in-5 (Section 5, three ternary weights in 5 bits): one thread per
@@ -111,7 +191,7 @@ __global__ __launch_bounds__(256) void pack_tri_kernel(PackParams p) {
     }
 }
 
-// Per-group metadata: (s, z) FP16 pairs [Q][N_pad]; per-tensor: FP32 (s, z).
+// Metadata of 3-in-5 weights: (s, 0) FP16 pairs [Q][N_pad]; per-tensor: FP32 (s, 0).
 __global__ __launch_bounds__(256) void pack_meta_kernel(PackParams p) {
     if (p.per_tensor) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -142,64 +222,27 @@ __global__ __launch_bounds__(256) void pack_meta_kernel(PackParams p) {
     }
 }
 
-// Fixed-point exponent E of column n for the exact K-split completion of FP partial
-// sums (split_complete_exact).  With the token scaled to |x| < 1 by the precompute, a
-// table entry (a signed sum of 4 activations) is below 4 in magnitude, stored as at
-// most 4 2^FIX_SHIFT, so one 128-block of bit-plane t adds at most |s'| 2^t 128 to a
-// partial sum and the zero-point term of a group is at most |s' z'| G (|S| <= G).
-// Their sum over the column's groups, B (with 1/16 added for the FP32 rounding of the
-// partial sums), bounds every split's partial sum and their total; E is the smallest
-// integer with B < 2^(BND_BITS + E).  (The fused split kernel, whose tables hold the
-// unscaled FP16 activations, |x| <= 65504 < 2^16, uses E + 16.)  E = 0 for padding
-// columns and all-zero scales; B is not finite only for non-finite scales, whose
-// outputs are unspecified on this path.
-__global__ __launch_bounds__(256) void pack_bound_kernel(PackParams p, float cs, float cz, float c0) {
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= p.N_pad) return;
-    int E = 0;
-    if (n < p.N) {
-        const double kpg = (double)(p.G / KBLK), planes = (double)((1 << p.bits) - 1), G = (double)p.G;
-        double B = 0.0;
-        for (int64_t q = 0; q < p.Q; ++q) {
-            float s, z;
-            if (p.per_tensor) {
-                s = ((const float *)p.meta)[0];
-                z = ((const float *)p.meta)[1];
-            } else {
-                const uint32_t w = ((const uint32_t *)p.meta)[q * p.N_pad + n];
-                s = __half2float(__ushort_as_half((unsigned short)(w & 0xFFFFu)));
-                z = __half2float(__ushort_as_half((unsigned short)(w >> 16)));
-            }
-            const double sp = (double)cs * (double)s, zp = (double)cz * (double)z + (double)c0;
-            B += kpg * fabs(sp) * 128.0 * planes + fabs(sp * zp) * G;
-        }
-        B *= 1.0625;
-        if (B > 0.0 && B <= 1e300) E = ilogb(B) + 1 - BND_BITS;
-    }
-    p.bnd[n] = E;
-}
-
 int launch_pack(const PackParams &p, void *stream) {
     hipStream_t s = (hipStream_t)stream;
-    int64_t total = p.N_pad * p.KB;
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 65535 * 16) blocks = 65535 * 16;
-    if (p.wfmt == LUTGEMM_WFMT_TERNARY_3IN5)
+    if (p.wfmt == LUTGEMM_WFMT_TERNARY_3IN5) {
+        int64_t blocks = (p.N_pad * p.KB + 255) / 256;
+        if (blocks > 65535 * 16) blocks = 65535 * 16;
         hipLaunchKernelGGL(pack_tri_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p);
-    else
-        hipLaunchKernelGGL(pack_planes_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-    int64_t mt = p.per_tensor ? 1 : p.Q * p.N_pad;
-    int64_t mblocks = (mt + 255) / 256;
-    if (mblocks > 65535 * 16) mblocks = 65535 * 16;
-    hipLaunchKernelGGL(pack_meta_kernel, dim3((unsigned)mblocks), dim3(256), 0, s, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-    if (p.wfmt == LUTGEMM_WFMT_TERNARY_3IN5) return (int)hipSuccess;
-    float cs, cz, c0;
-    format_consts(p.wfmt, p.bits, cs, cz, c0);
-    hipLaunchKernelGGL(pack_bound_kernel, dim3((unsigned)((p.N_pad + 255) / 256)), dim3(256), 0, s, p, cs, cz, c0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return (int)e;
+        const int64_t mt = p.per_tensor ? 1 : p.Q * p.N_pad;
+        int64_t mblocks = (mt + 255) / 256;
+        if (mblocks > 65535 * 16) mblocks = 65535 * 16;
+        hipLaunchKernelGGL(pack_meta_kernel, dim3((unsigned)mblocks), dim3(256), 0, s, p);
+        return (int)hipGetLastError();
+    }
+    BoundConsts k;
+    format_consts(p.wfmt, p.bits, k.cs, k.cz, k.c0);
+    const uint32_t plane_wgs = (uint32_t)((p.N_pad / 64 * p.KB + 3) / 4);
+    const dim3 grid(plane_wgs + (uint32_t)((p.N_pad + 255) / 256));
+    if (p.bits == 1) hipLaunchKernelGGL(pack_kernel<1>, grid, dim3(256), 0, s, p, plane_wgs, k);
+    else if (p.bits == 2) hipLaunchKernelGGL(pack_kernel<2>, grid, dim3(256), 0, s, p, plane_wgs, k);
+    else hipLaunchKernelGGL(pack_kernel<4>, grid, dim3(256), 0, s, p, plane_wgs, k);
     return (int)hipGetLastError();
 }
 
