@@ -176,8 +176,7 @@ lutgemm_status_t lutgemm_table_offsets(const lutgemm_problem_t *problem, int64_t
  * leaves them zero again (the kernel re-arms them) and nothing else is ever stored
  * there, so one zero fill per allocation suffices even when the workspace is shared
  * by calls on different problems.  A workspace must not be shared by calls that
- * run concurrently.  With several tokens (ACT_FP16, M >= 16, see
- * lutgemm_mpgemm) the size covers the matrix-core evaluation (its prepared activations and partial sums); a smaller
+ * run concurrently.  With several tokens (see lutgemm_mpgemm) the size covers the matrix-core evaluation (its prepared activations and partial sums); a smaller
  * workspace that still holds the lookup kernels' partial sums (none, if those do not
  * split K) is accepted and runs the lookup kernels.
  */
@@ -232,12 +231,13 @@ lutgemm_status_t lutgemm_precompute(const lutgemm_problem_t *problem, int64_t M,
  *   workspace  device, workspace_bytes >= lutgemm_workspace_size(problem, M);
  *              may be NULL when that size is 0
  * FP path: O = t_m sum_q s'_q (sum_b 2^b sum_j L_{b,j} - z'_q S_q), FP32.
- * With several tokens (ACT_FP16; UINT weights with group scales: M >= 16 and M N <= 2^24;
+ * With several tokens (ACT_INT8: M >= 5.  ACT_FP16; UINT weights with group scales: M >= 16 and M N <= 2^24;
  * other UINT weights of 2 or 4 bits: 16 <= M <= 64, or M >= 16 and M N <= 2^20; other
  * weights: 16 <= M <= 32) the sums of lookups are evaluated on the matrix cores: an entry
  * is a signed sum of its 4 activations (Eq. 5), so the lookups of a column add up to the
- * dot product of its codes with the activations, which are recovered from the tables.
- * The tables must be half tables as the layout defines.
+ * dot product of its codes with the activations, which are recovered from the tables
+ * (ACT_INT8: exactly, so the result is the same).  The tables must be half tables as the
+ * layout defines.
  * INT8 path: acc = sum_k q_a w exactly; O = acc (INT32) or (float(acc) s_a) s_w.
  * TERNARY_3IN5: O = t_m s (sum_j L_j) (FP path, FP32) with one lookup per triple.
  * The result is bitwise reproducible run to run.
@@ -289,18 +289,18 @@ size_t lutgemm_fused_workspace_size(const lutgemm_problem_t *problem, int64_t M)
  * activations as given (no token scaling, no FP16 rounding of entries), plus the
  * split sum; with larger weights and ACT_INT8 the same kernel, each workgroup
  * reading the whole token for the absmax and building the exact INT16 entries of
- * the precompute's quantization for its K range.  Several tokens with ACT_FP16: the calls
- * that lutgemm_mpgemm evaluates on the matrix cores run there on the activations
- * themselves (codes and activations are exact in FP16, scales and zero points are applied
- * in FP32); else, with 2 < M <= 64 on layers of at most 64 x 256 columns, the multi-token kernel reads the FP16 activations
- * of its tokens and K range, scales each token by the power of two 2^-e with e from its
- * absmax over that K range, and builds the same FP16 entries as lutgemm_precompute
+ * the precompute's quantization for its K range.  Several tokens: the calls that
+ * lutgemm_mpgemm evaluates on the matrix cores (ACT_INT8: all with M >= 3) run there on the
+ * activations themselves (ACT_FP16: codes and activations are exact in FP16, scales and
+ * zero points are applied in FP32; ACT_INT8: the precompute's quantizer).  Else, ACT_FP16
+ * with 2 < M <= 64 on layers of at most 64 x 256 columns, the multi-token kernel reads the
+ * FP16 activations of its tokens and K range, scales each token by the power of two 2^-e
+ * with e from its absmax over that K range, and builds the same FP16 entries as lutgemm_precompute
  * (tuning key LUTGEMM_TUNE_MT_FUSED forces it on or off; every column tile repeats the
  * build, so beyond those sizes precompute + mpGEMM is faster).  TERNARY_3IN5: one kernel
  * for every M, tables built per workgroup for its token.  Otherwise (larger N with
- * ACT_FP16, ACT_INT8 with M > 2, ACT_FP16_LUT8) it runs lutgemm_precompute into the
- * workspace followed by lutgemm_mpgemm: with several tokens every workgroup would have to
- * read all of its tokens for the INT8 quantizer's absmax.
+ * ACT_FP16, ACT_FP16_LUT8, a workspace too small for the matrix cores) it runs
+ * lutgemm_precompute into the workspace followed by lutgemm_mpgemm.
  *   act        device FP16 [M][K]
  *   packed, out, out_dtype, accumulate   as for lutgemm_mpgemm
  *   workspace  device, workspace_bytes >= lutgemm_fused_workspace_size(problem, M);
@@ -399,7 +399,7 @@ enum {
                                        integer (INT8 activations, or FP16 activations on weights with
                                        one scale per column or tensor); 0 always sums FP32 partials
                                        in split order (1)                                            */
-    LUTGEMM_TUNE_MFMA = 17,         /* LUTGEMM_MFMA: several tokens (M > 2, ACT_FP16) on the matrix
+    LUTGEMM_TUNE_MFMA = 17,         /* LUTGEMM_MFMA: several tokens (M > 2) on the matrix
                                        cores: 0 never (the lookup kernels), 1 always (-1: planned;
                                        also off while a key of the multi-token lookup kernel, MT_* or
                                        MT4 / MT16, is away from its default)                        */

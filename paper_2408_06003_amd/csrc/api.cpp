@@ -326,19 +326,22 @@ LutPlan plan_lut(const Layout &L, int64_t M, bool fused) {
     return P;
 }
 
-// Which FP16 calls go to the matrix cores.  They win from 16 tokens on (graph replays, us,
-// lookups -> matrix cores: INT4 4096 x 12288 33 -> 20 at M = 16, 273 -> 60 at 256, 1004 ->
-// 151 at 1024; the smallest gain, INT4 11008 x 300 two-call at 16 tokens, 22.4 -> 21.3; at 8
-// tokens three launches against two lose on small layers, INT4 4096 x 1024 12.1 -> 13.0).
-// They are also the more exact path, by so much that a call's result would move: the lookup
-// kernel's FP16 word sums are off by 4.6-7.6e-4 (relative), and over many outputs with one
-// scale per column or tensor, where no group scales average them, its largest deviation
+// Which calls go to the matrix cores.  INT8 activations (exact, so the same bits): from 3
+// tokens on where the activations are given, from 5 on from tables (graph replays, us,
+// lookups -> matrix cores: ternary 4096 x 4096 fused 12.5 -> 10.5 at M = 3, 29.3 -> 15.3 at
+// 64, 375 -> 64 at 2048; from tables 12.1 -> 13.1 at 3, 15.1 -> 13.8 at 5).  FP16 activations
+// win from 16 tokens on (INT4 4096 x 4096 18.5 -> 14.0 at M = 16, 112 -> 35 at 256, 679 ->
+// 100 at 2048; at 8 tokens three launches against two lose on small layers, 12.6 -> 13.5).
+// There they are also the more exact path, by so much that a call's result would move: the
+// lookup kernel's FP16 word sums are off by 4.6-7.6e-4 (relative), and over many outputs with
+// one scale per column or tensor, where no group scales average them, its largest deviation
 // exceeds 1e-2 of the output's rms (24 seeds each, deviations over 1e-2: binary 8192 columns
 // 0 / 0 / 1 / 6 at 16 / 32 / 64 / 256 tokens; ternary 0 / 0 / 1 / 3; INT2 per channel 0 up to
 // 64, 2 at 256; INT4 and INT2 groups of 128 at most 1 up to 2^24 outputs).  A caller that
 // compares with stored results must not see more than that from a choice of kernel, so
-// larger calls of those kinds stay with the lookups.
-static bool mfma_planned(const Layout &L, int64_t M) {
+// larger FP16 calls of those kinds stay with the lookups.
+static bool mfma_planned(const Layout &L, int64_t M, bool fused) {
+    if (L.act == LUTGEMM_ACT_INT8) return M >= (fused ? 3 : 5);
     if (M < 16) return false;
     if (L.wfmt == LUTGEMM_WFMT_UINT && L.Q > 1) return M * L.N <= (int64_t)1 << 24;
     if (L.bits > 1 && L.wfmt == LUTGEMM_WFMT_UINT) return M <= 64 || M * L.N <= (int64_t)1 << 20;
@@ -346,19 +349,22 @@ static bool mfma_planned(const Layout &L, int64_t M) {
 }
 
 // Tile (tokens per workgroup) of the matrix-core plan: a larger one decodes each weight for
-// more tokens, a smaller one gives more workgroups.  With group scales (the dearer decode)
-// 128 tokens win from 192 such tiles on and 64 from 96 (INT4 4096 x 12288, tiles of 32 / 64 /
-// 128: 44 / 39 / 46 us at M = 128, 97 / 95 / 93 at 512); without, from 512 and 512 (binary:
-// 62 / 68 / 81 at 512, 113 / 106 / 123 at 1024).  K is split to two workgroups per CU, at
+// more tokens, a smaller one gives more workgroups and so fewer K splits.  With group scales
+// (the dearer decode) 128 tokens win from 96 such tiles on and 64 from 47 (INT4, tiles of
+// 32 / 64 / 128, us: 4096 x 4096 68 / 57 / 54 at M = 700, 25 / 25 / 29 at 100; 2432 x 11973
+// 31 / 29 / 30 at 100, 43 / 43 / 42 at 256); without, 64 from 512 tiles on and 128 from 700
+// (INT2 per channel 2432 x 11973 31 / 37 / 37 at 256, 64 / 60 / 69 at 700, 145 / 124 / 119 at
+// 2048); INT8 never 128 (110 / 108 / 131 there).  K is split to two workgroups per CU, at
 // least 4 blocks each.
-LutPlan plan_mfma(const Layout &L, int64_t M) {
+LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     LutPlan P{};
     P.kind = -1;
     const int force = tuning(LUTGEMM_TUNE_MFMA);
-    if (L.act != LUTGEMM_ACT_FP16 || L.tri || M <= 2 || force == 0) return P;
+    if (L.act == LUTGEMM_ACT_FP16_LUT8 || L.tri || M <= 2 || force == 0) return P;
+    const bool i8 = L.act == LUTGEMM_ACT_INT8;
     // overrides of the multi-token lookup kernel select that kernel
     if (force < 0) {
-        if (!mfma_planned(L, M)) return P;
+        if (!mfma_planned(L, M, fused)) return P;
         for (const int key : {LUTGEMM_TUNE_MT16, LUTGEMM_TUNE_MT_TARGET, LUTGEMM_TUNE_MT_SPLITS, LUTGEMM_TUNE_MT_ORDER,
                               LUTGEMM_TUNE_MT_FUSED, LUTGEMM_TUNE_MT4})
             if (tuning(key) != kTuneDefault[key]) return P;
@@ -367,7 +373,7 @@ LutPlan plan_mfma(const Layout &L, int64_t M) {
     P.n_tiles = L.N_pad / NTILE;
     auto tiles = [&](int mt) { return P.n_tiles * ((M + mt - 1) / mt); };
     const bool grp = L.Q > 1;
-    P.mt = tiles(128) >= (grp ? 192 : 512) ? 128 : tiles(64) >= (grp ? 96 : 512) ? 64 : 32;
+    P.mt = !i8 && tiles(128) >= (grp ? 96 : 700) ? 128 : tiles(64) >= (grp ? 47 : 512) ? 64 : 32;
     if (M <= 64 && P.mt == 128) P.mt = 64;
     if (M <= 32) P.mt = 32;
     const int tile = tuning(LUTGEMM_TUNE_MFMA_TILE);
@@ -380,12 +386,15 @@ LutPlan plan_mfma(const Layout &L, int64_t M) {
     const int fs = tuning(LUTGEMM_TUNE_MFMA_SPLITS);
     if (fs > 0) splits = fs < L.KB ? fs : L.KB;
     P.kbs = (int)((L.KB + splits - 1) / splits);
+    if (i8 && (P.kbs & 1)) ++P.kbs;  // whole steps of two blocks
     P.splits = (int)((L.KB + P.kbs - 1) / P.kbs);
     P.order = 8;
     P.part_off = CNT_AREA;
     P.prep_off = CNT_AREA + (P.splits > 1 ? align256((size_t)P.splits * P.m_tiles * P.mt * L.N_pad * 4) : 0);
-    P.prep_s_off = P.prep_off + align256((size_t)P.m_tiles * P.mt * L.K * 2);  // whole token tiles
-    P.ws_bytes = P.prep_s_off + align256((size_t)M * L.Q * 4);
+    P.prep_s_off = P.prep_off + (i8 ? (size_t)P.m_tiles * P.mt * align256((size_t)L.K)  // whole token tiles
+                                    : align256((size_t)P.m_tiles * P.mt * L.K * 2));
+    P.prep_t_off = P.prep_s_off + align256((size_t)M * L.Q * 4);
+    P.ws_bytes = P.prep_t_off + (i8 ? align256((size_t)M * 4) : 0);
     return P;
 }
 
@@ -440,8 +449,11 @@ static lutgemm_status_t run_mfma(const Layout &L, const LutPlan &plan, int64_t M
     char *ws = (char *)workspace;
     LutParams lp = lut_params(L, plan, M, tables, packed, out, out_dtype, accumulate, workspace);
     lp.act = (const uint16_t *)act;
-    float *S = L.wfmt != LUTGEMM_WFMT_BINARY ? (float *)(ws + plan.prep_s_off) : nullptr;
-    int e = launch_mfma_prep(lp, L, ws + plan.prep_off, S, stream);
+    const bool i8 = L.act == LUTGEMM_ACT_INT8;
+    void *S = i8 || L.wfmt != LUTGEMM_WFMT_BINARY ? ws + plan.prep_s_off : nullptr;
+    float *tok = i8 && act ? (float *)(ws + plan.prep_t_off) : nullptr;
+    int e = launch_mfma_prep(lp, L, ws + plan.prep_off, S, tok, stream);
+    if (tok) lp.tok = tok;
     lp.act = (const uint16_t *)(ws + plan.prep_off);
     lp.S = S;
     if (e == 0) e = launch_mfma(lp, L, plan, stream);
@@ -467,7 +479,7 @@ struct FusedScratch {
 // Scratch of lutgemm_mpgemm: what the planned kernels need, and at least what the lookup
 // kernels need (they run on a workspace too small for the matrix-core path).
 static size_t lut_ws_bytes(const Layout &L, int64_t M) {
-    const size_t lookup = plan_lut(L, M).ws_bytes, mfma = plan_mfma(L, M).ws_bytes;
+    const size_t lookup = plan_lut(L, M).ws_bytes, mfma = plan_mfma(L, M, false).ws_bytes;
     return lookup > mfma ? lookup : mfma;
 }
 
@@ -634,7 +646,7 @@ lutgemm_status_t lutgemm_mpgemm(const lutgemm_problem_t *problem, int64_t M, con
     if (out_dtype == LUTGEMM_OUT_INT32 && problem->act != LUTGEMM_ACT_INT8) return LUTGEMM_ERROR_NOT_SUPPORTED;
     if (accumulate != 0 && accumulate != 1) return LUTGEMM_ERROR_INVALID_VALUE;
     Layout L = make_layout(*problem);
-    const LutPlan mp = plan_mfma(L, M);
+    const LutPlan mp = plan_mfma(L, M, false);
     if (mp.kind == 4 && workspace && aligned16(workspace) && workspace_bytes >= mp.ws_bytes) {
         if (tuning(LUTGEMM_TUNE_LOG)) log_plan("lutgemm_mpgemm", L, mp, M);
         return run_mfma(L, mp, M, tables, nullptr, packed, out, out_dtype, accumulate, workspace, stream);
@@ -653,11 +665,11 @@ size_t lutgemm_fused_workspace_size(const lutgemm_problem_t *problem, int64_t M)
     if (check_problem(problem, M) != LUTGEMM_SUCCESS) return 0;
     Layout L = make_layout(*problem);
     const FusedScratch fs = fused_scratch(L, plan_lut(L, M, true), M);
-    const size_t mfma = plan_mfma(L, M).ws_bytes;
+    const size_t mfma = plan_mfma(L, M, true).ws_bytes;
     if (mfma == 0) return fs.total;
     // (the precompute + mpGEMM form: its tables come after the whole workspace)
-    if (!fs.fused) return align256(lut_ws_bytes(L, M)) + fs.tables;
-    return fs.total > mfma ? fs.total : mfma;
+    const size_t two_call = fs.fused ? fs.total : align256(lut_ws_bytes(L, M)) + fs.tables;
+    return two_call > mfma ? two_call : mfma;
 }
 
 lutgemm_status_t lutgemm_mpgemm_fused(const lutgemm_problem_t *problem, int64_t M, const void *act,
@@ -672,7 +684,7 @@ lutgemm_status_t lutgemm_mpgemm_fused(const lutgemm_problem_t *problem, int64_t 
     if (out_dtype == LUTGEMM_OUT_INT32 && problem->act != LUTGEMM_ACT_INT8) return LUTGEMM_ERROR_NOT_SUPPORTED;
     if (accumulate != 0 && accumulate != 1) return LUTGEMM_ERROR_INVALID_VALUE;
     Layout L = make_layout(*problem);
-    const LutPlan mp = plan_mfma(L, M);
+    const LutPlan mp = plan_mfma(L, M, true);
     if (mp.kind == 4 && workspace && aligned16(workspace) && workspace_bytes >= mp.ws_bytes) {
         if (tuning(LUTGEMM_TUNE_LOG)) log_plan("lutgemm_mpgemm_fused", L, mp, M);
         return run_mfma(L, mp, M, nullptr, act, packed, out, out_dtype, accumulate, workspace, stream);

@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "lut_common.h"
 #include "mfma_common.h"
 
@@ -94,6 +96,81 @@ __global__ __launch_bounds__(256) void prep_kernel(const void *src, uint4 *dst, 
     }
 }
 
+// The INT8 path: INT8 activations in the order of mfma_decode_i8 (register s, byte i:
+// activation 8 i + 4 (s / 4) + 3 - s % 4 of the word), rows padded with zeros to KP (a
+// multiple of 256), and their sum per token.  From FP16 activations: the quantizer of
+// lutgemm_precompute and the token factor t; from INT16 half tables (TAB): x_3 = (T[1] -
+// T[0]) / 2 and so on, exactly.
+template <bool TAB>
+__global__ __launch_bounds__(256) void prep_i8_kernel(const void *src, uint4 *dst, int *S, float *tok, int64_t K, int64_t KP) {
+    __shared__ float redm[4];
+    __shared__ int reds[4];
+    const int64_t m = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    const uint4 *a = (const uint4 *)((const uint16_t *)src + m * K);
+    float scale = 0.f;
+    if constexpr (!TAB) {
+        float amax = 0.f;
+        for (int64_t c = tid; c < K / 8; c += blockDim.x) {
+            const uint4 v = a[c];
+            amax = fmaxf(amax, fmaxf(absmax4(make_uint2(v.x, v.y)), absmax4(make_uint2(v.z, v.w))));
+        }
+        amax = wave_max(amax);
+        if (lane == 63) redm[wave] = amax;
+        __syncthreads();
+        amax = redm[0];
+        for (int w = 1; w < waves; ++w) amax = fmaxf(amax, redm[w]);
+        if (amax != 0.f) scale = __fdiv_rn(127.0f, amax);
+        if (tid == 0) tok[m] = amax != 0.f ? __fdiv_rn(amax, 127.0f) : 0.f;
+    }
+    int sum = 0;
+    for (int64_t w = tid; w < KP / 32; w += blockDim.x) {
+        uint32_t r[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+        if (w < K / 32) {
+            int x[32];
+            if constexpr (TAB) {
+                const uint4 *T = (const uint4 *)src + m * (K / 4) + 8 * w;
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    const uint4 e = T[g];
+                    const int t0 = (int16_t)(e.x & 0xFFFFu), t1 = (int)e.x >> 16, t2 = (int16_t)(e.y & 0xFFFFu), t4 = (int16_t)(e.z & 0xFFFFu);
+                    x[4 * g + 3] = (t1 - t0) >> 1;
+                    x[4 * g + 2] = (t2 - t0) >> 1;
+                    x[4 * g + 1] = (t4 - t0) >> 1;
+                    x[4 * g] = -t0 - x[4 * g + 1] - x[4 * g + 2] - x[4 * g + 3];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint4 v = a[4 * w + i];
+                    const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        x[8 * i + 2 * j] = (int)fminf(fmaxf(rintf(h2f(h[j] & 0xFFFFu) * scale), -127.f), 127.f);
+                        x[8 * i + 2 * j + 1] = (int)fminf(fmaxf(rintf(h2f(h[j] >> 16) * scale), -127.f), 127.f);
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 32; ++k) {
+                sum += x[k];
+                r[(k & 4) + 3 - (k & 3)] |= ((uint32_t)x[k] & 0xFFu) << (8 * (k >> 3));
+            }
+        }
+        uint4 *d = dst + (m * KP) / 16 + 2 * w;
+        d[0] = make_uint4(r[0], r[1], r[2], r[3]);
+        d[1] = make_uint4(r[4], r[5], r[6], r[7]);
+    }
+    sum = wave_sum_i(sum);
+    if (lane == 63) reds[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        int t = reds[0];
+        for (int w = 1; w < waves; ++w) t += reds[w];
+        S[m] = t;
+    }
+}
+
 // ---------------------------------------------------------------- large M
 //
 // Workgroup tile 32 MS (tokens) x 256 (columns), 4 wavefronts of 32 MS x 64, K step one
@@ -107,8 +184,15 @@ __global__ __launch_bounds__(256) void prep_kernel(const void *src, uint4 *dst, 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void glb_void;
 
-template <int BITS, bool GRP, int MS>
+// INT8: v_mfma_i32_32x32x32_i8 on INT8 activations and the codes q themselves, two
+// 128-blocks per step (the same 256 bytes per row), exact INT32 sums; sum q x and the
+// activation sum S give the dot product (binary: 2 sum - S, ternary: sum - S).
+template <int BITS, bool GRP, int MS, bool INT8>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void mfma_gemm_kernel(LutParams p, int wfmt, uint32_t n_tiles, uint32_t m_tiles, int order) {
+    static_assert(!(INT8 && GRP), "INT8 activations: one scale per column or tensor");
+    typedef std::conditional_t<INT8, intx4_t, half8_t> Frag;
+    typedef std::conditional_t<INT8, intx16_t, floatx16_t> Acc;
+    constexpr int BPS = INT8 ? 2 : 1;  // 128-blocks per step
     constexpr int ROWS = 32 * MS;
     constexpr int CP = GRP ? 2 : 4, NP = 8 / CP;  // MFMAs per part of a chain, parts per chain
     __shared__ __attribute__((aligned(16))) char A0[ROWS * 256], A1[ROWS * 256];
@@ -122,38 +206,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
     const int kbA = tl.split * p.kbs;
     const int kbB = kbA + p.kbs < (int)p.KB ? kbA + p.kbs : (int)p.KB;
 
-    floatx16_t acc[MS][2];
+    Acc acc[MS][2];
 #pragma unroll
     for (int i = 0; i < MS; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-    // activations of block kb into dst: each instruction fills 4 rows (1 KiB); the tile's
-    // rows past M are scratch (their sums are never stored)
-    const uint32_t rowb = (uint32_t)p.K * 2u;
-    const __amdgpu_buffer_rsrc_t rA = buf_rsrc((const char *)p.act + m0 * p.K * 2, ROWS * rowb);
+    // activations of the step at block kb into dst: each instruction fills 4 rows (1 KiB);
+    // the tile's rows past M are scratch (their sums are never stored)
+    const uint32_t rowb = INT8 ? ((uint32_t)p.K + 255u) & ~255u : (uint32_t)p.K * 2u;
+    const __amdgpu_buffer_rsrc_t rA = buf_rsrc((const char *)p.act + m0 * rowb, ROWS * rowb);
     const uint32_t avo = (uint32_t)(lane >> 4) * rowb + 16u * (uint32_t)((lane & 15) ^ (lane >> 4));  // (rowb % 256 = 0)
     auto load_act = [&](int kb, char *dst) {
 #pragma unroll
         for (int i = 0; i < 2 * MS; ++i) {
             const int row0 = wave * 8 * MS + 4 * i;  // row0 % 16 = 4 (row0 / 4 % 4)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void *)(dst + row0 * 256), 16, (int)(avo ^ (64u * ((2 * MS * wave + i) & 3))),
-                                                     (int)((uint32_t)row0 * rowb + (uint32_t)kb * 256u), 0, 0);
+                                                     (int)((uint32_t)row0 * rowb + (uint32_t)kb * (256u / BPS)), 0, 0);
         }
     };
     int q_cur = GRP ? kbA / p.kpg : 0;  // quantization group of the last block loaded
     struct W {
-        uint2 w[BITS];
+        uint2 w[BPS][BITS];
         uint32_t m;
     };
-    // words and metadata of n-sub j of block kb
+    // words and metadata of n-sub j of the step at block kb (a second block past K: the
+    // first's words, against zero activations)
     auto load_w = [&](int kb, int j, W &w) {
-        const __amdgpu_buffer_rsrc_t rW =
-            buf_rsrc(p.planes + (int64_t)kb * BITS * p.N_pad, (uint32_t)BITS * (uint32_t)p.N_pad * 16u);
 #pragma unroll
-        for (int t = 0; t < BITS; ++t) w.w[t] = buf_u64(rW, n0 * 16u + 8u * lg + 512u * j, (uint32_t)t * (uint32_t)p.N_pad * 16u);
+        for (int bb = 0; bb < BPS; ++bb) {
+            const int kc = kb + bb < (int)p.KB ? kb + bb : kb;
+            const __amdgpu_buffer_rsrc_t rW =
+                buf_rsrc(p.planes + (int64_t)kc * BITS * p.N_pad, (uint32_t)BITS * (uint32_t)p.N_pad * 16u);
+#pragma unroll
+            for (int t = 0; t < BITS; ++t) w.w[bb][t] = buf_u64(rW, n0 * 16u + 8u * lg + 512u * j, (uint32_t)t * (uint32_t)p.N_pad * 16u);
+        }
         if constexpr (GRP) {
             if (j == 0 && kb >= (q_cur + 1) * p.kpg) ++q_cur;  // blocks are loaded in order
             const __amdgpu_buffer_rsrc_t rM = buf_rsrc((const uint32_t *)p.meta + (int64_t)q_cur * p.N_pad, (uint32_t)p.N_pad * 4u);
@@ -205,30 +294,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
     auto step = [&](int kb, const char *as, char *as_n) {
         __builtin_amdgcn_s_waitcnt(0);  // this wavefront's loads have landed (direct LDS ones included)
         __syncthreads();                // ... and all others'; every wavefront is done with the other buffer
-        const int kn = kb + 1 < kbB ? kb + 1 : kb;
+        const int kn = kb + BPS < kbB ? kb + BPS : kb;
         load_act(kn, as_n);
         // GRP: a block's sums are scaled into the accumulators half a chain after their last
         // MFMA, while the next chain runs
-        floatx16_t tmp[2];
+        Acc tmp[2];
         float scs[2] = {0.f, 0.f};
         auto scale = [&](int c) {  // chain c = MS j + i
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[c % MS][c / MS][v] = fmaf(scs[c / MS], tmp[c & 1][v], acc[c % MS][c / MS][v]);
+            for (int v = 0; v < 16; ++v) acc[c % MS][c / MS][v] = fmaf(scs[c / MS], (float)tmp[c & 1][v], (float)acc[c % MS][c / MS][v]);
         };
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            half8_t b[8];
+            Frag b[8];
             W &w = j ? w1 : w0;
-            mfma_decode<BITS>(w.w, b);
+            if constexpr (INT8) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {  // word u % 2 of block u / 2
+                    uint32_t ww[BITS];
+#pragma unroll
+                    for (int t = 0; t < BITS; ++t) ww[t] = (u & 1) ? w.w[u >> 1][t].y : w.w[u >> 1][t].x;
+                    intx4_t d[2];
+                    mfma_decode_i8<BITS>(ww, d);
+                    b[2 * u] = d[0];
+                    b[2 * u + 1] = d[1];
+                }
+            } else {
+                mfma_decode<BITS>(w.w[0], b);
+            }
             if constexpr (GRP) scs[j] = v_scale<BITS>(wfmt, w.m).sc;
             load_w(kn, j, w);
             // operand reads run CP MFMAs ahead
-            half8_t a[2][CP];
-            auto read_a = [&](int h, half8_t(&d)[CP]) {  // part h % NP of chain h / NP
+            Frag a[2][CP];
+            auto read_a = [&](int h, Frag(&d)[CP]) {  // part h % NP of chain h / NP
                 const int row = 32 * (h / NP) + lc;
 #pragma unroll
-                for (int f = 0; f < CP; ++f)
-                    d[f] = *(const half8_t *)(as + row * 256 + 16 * ((8 * lg + CP * (h % NP) + f) ^ (row & 15)));
+                for (int f = 0; f < CP; ++f) {
+                    const int ff = CP * (h % NP) + f;
+                    const int chunk = INT8 ? 8 * (ff >> 2) + 4 * lg + (ff & 3) : 8 * lg + ff;
+                    d[f] = *(const Frag *)(as + row * 256 + 16 * (chunk ^ (row & 15)));
+                }
             };
             read_a(0, a[0]);
 #pragma unroll
@@ -243,6 +348,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
                     for (int f = 0; f < CP; ++f)
                         tmp[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[h & 1][f], b[CP * (h % NP) + f], tmp[c & 1], 0, 0, 0);
                     if (h % NP == NP / 2 && c > 0) scale(c - 1);
+                } else if constexpr (INT8) {
+#pragma unroll
+                    for (int f = 0; f < CP; ++f)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[h & 1][f], b[CP * (h % NP) + f], acc[i][j], 0, 0, 0);
                 } else {
 #pragma unroll
                     for (int f = 0; f < CP; ++f)
@@ -258,29 +367,77 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
     load_w(kbA, 0, w0);
     load_w(kbA, 1, w1);
     int kb = kbA;
-    for (; kb + 1 < kbB; kb += 2) {
+    for (; kb + BPS < kbB; kb += 2 * BPS) {
         step(kb, A0, A1);
-        step(kb + 1, A1, A0);
+        step(kb + BPS, A1, A0);
     }
     if (kb < kbB) step(kb, A0, A1);
+    __builtin_amdgcn_s_waitcnt(0);  // the last step's prefetch has landed: LDS is quiet from here on
 
     // Epilogue.  The lane holds column lane % 32, rows 8 (v / 4) + 4 (lane / 32) + v % 4 of
-    // each 32 x 32 block; 16 rows of the wavefront's 64 columns at a time go through LDS so
-    // that a row leaves in one store of 64 consecutive columns and the row's operands are
-    // uniform.
-    __builtin_amdgcn_s_waitcnt(0);  // (the last step's prefetch has landed)
-    __syncthreads();                // the activation buffers are free
-    float *ew = (float *)E + wave * (16 * 64);
+    // each 32 x 32 block.
+    typedef std::conditional_t<INT8, int, float> Out;
+    const bool zero_term = INT8 || (!GRP && wfmt != LUTGEMM_WFMT_BINARY);  // (GRP: added above)
+    if (p.splits > 1) {
+        // partial sums: 128-byte rows straight from the registers (the tile's rows past M are
+        // allocated); what belongs to the whole K is added by the first split
+        const int64_t m_alloc = (int64_t)m_tiles * ROWS;
+        Out *part = (Out *)p.part + ((int64_t)tl.split * m_alloc + m0) * p.N_pad + n0;
+        float sc[2] = {1.f, 1.f}, nsz[2] = {0.f, 0.f};
+        if constexpr (!GRP && !INT8) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const VScale s = p.per_tensor ? v_scale_f<BITS>(wfmt, ((const float *)p.meta)[0], ((const float *)p.meta)[1])
+                                              : v_scale<BITS>(wfmt, ((const uint32_t *)p.meta)[n0 + 32 * j]);
+                sc[j] = s.sc;
+                nsz[j] = -(s.sc * s.zo);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MS; ++i) {
+            Out S[16];
+            if (zero_term && tl.split == 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int64_t m = m0 + 32 * i + 8 * (v >> 2) + 4 * lg + (v & 3);
+                    S[v] = ((const Out *)p.S)[m < p.M ? m : p.M - 1];
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) S[v] = 0;
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                Out *row = part + (int64_t)(32 * i + 8 * (v >> 2) + 4 * lg + (v & 3)) * p.N_pad;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    Out y = acc[i][j][v];
+                    if constexpr (INT8) y = 2 * y - S[v] * (wfmt == LUTGEMM_WFMT_TERNARY ? 2 : 1);
+                    else if constexpr (!GRP) y = fmaf(nsz[j], S[v], y * sc[j]);
+                    row[32 * j] = y;
+                }
+            }
+        }
+        return;
+    }
+    // outputs: 16 rows of the wavefront's 64 columns at a time go through LDS so that a row
+    // leaves in one store of 64 consecutive columns and its operands are uniform; whole
+    // groups of rows read all their operands before the first store
+    __syncthreads();  // the activation buffers are free
+    Out *ew = (Out *)E + wave * (16 * 64);
     const int64_t n = (int64_t)tl.nt * NTILE + wave * 64 + lane;  // column of this lane from here on
     float sc = 1.f, nsz = 0.f;
-    if constexpr (!GRP) {
+    if constexpr (!GRP && !INT8) {
         const VScale s = p.per_tensor ? v_scale_f<BITS>(wfmt, ((const float *)p.meta)[0], ((const float *)p.meta)[1])
                                       : v_scale<BITS>(wfmt, ((const uint32_t *)p.meta)[n]);
         sc = s.sc;
         nsz = -(s.sc * s.zo);
     }
-    const bool zero_term = !GRP && wfmt != LUTGEMM_WFMT_BINARY && tl.split == 0;  // whole K: the first split adds it
-    const int64_t m_alloc = (int64_t)m_tiles * ROWS;
+    auto finish = [&](Out y, Out S) {  // S: the row's activation sum (0 where it does not enter)
+        if constexpr (INT8) return 2 * y - S * (wfmt == LUTGEMM_WFMT_TERNARY ? 2 : 1);  // as store_out expects it
+        else if constexpr (!GRP) return fmaf(nsz, S, y * sc);
+        else return y;
+    };
 #pragma unroll
     for (int i = 0; i < MS; ++i)
 #pragma unroll
@@ -292,19 +449,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
             const int64_t mr = m0 + 32 * i + 16 * h;
             const int rows = (int)(p.M - mr < 16 ? (p.M - mr < 0 ? 0 : p.M - mr) : 16);
-#pragma unroll 1
-            for (int r = 0; r < rows; ++r) {
-                float y = ew[r * 64 + lane];
-                const int64_t m = mr + r;
-                if constexpr (!GRP) {
-                    y *= sc;
-                    if (zero_term) y = fmaf(nsz, ((const float *)p.S)[m], y);
+            if (!INT8 && rows == 16 && !p.accumulate) {
+                Out y[16];
+                float tok[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    y[r] = finish(ew[r * 64 + lane], zero_term ? ((const Out *)p.S)[mr + r] : (Out)0);
+                    tok[r] = p.tok ? p.tok[mr + r] : 1.f;
                 }
-                if (p.splits > 1) {
-                    p.part[((int64_t)tl.split * m_alloc + m) * p.N_pad + n] = y;
-                } else if (n < p.N) {
-                    const Epi ep = load_epi<false>(p, wfmt, m, n, false);
-                    store_out<false>(p, wfmt, m, n, y, 0, ep);
+                if (n < p.N) {
+                    if (p.out_dtype == LUTGEMM_OUT_FP16) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ((__half *)p.out)[(mr + r) * p.N + n] = __float2half_rn(tok[r] * (float)y[r]);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ((float *)p.out)[(mr + r) * p.N + n] = tok[r] * (float)y[r];
+                    }
+                }
+            } else {
+#pragma unroll 4
+                for (int r = 0; r < rows; ++r) {
+                    const int64_t m = mr + r;
+                    const Out y = finish(ew[r * 64 + lane], zero_term ? ((const Out *)p.S)[m] : (Out)0);
+                    if (n < p.N) {
+                        const Epi ep = load_epi<INT8>(p, wfmt, m, n, false);
+                        store_out<INT8>(p, wfmt, m, n, INT8 ? 0.f : (float)y, INT8 ? (int)y : 0, ep);
+                    }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
@@ -317,16 +487,27 @@ template <int BITS, int MS>
 static void launch_mfma_ms(const LutParams &p, const Layout &L, const LutPlan &plan, hipStream_t s) {
     const dim3 grid((unsigned)(plan.n_tiles * plan.m_tiles * plan.splits));
     const uint32_t nt = (uint32_t)plan.n_tiles, mt = (uint32_t)plan.m_tiles;
-    if (L.Q > 1)
-        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, true, MS>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
-    else
-        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, false, MS>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+    if (L.act == LUTGEMM_ACT_INT8) {
+        if constexpr (BITS <= 2)
+            hipLaunchKernelGGL((mfma_gemm_kernel<BITS, false, MS, true>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+    } else if (L.Q > 1) {
+        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, true, MS, false>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+    } else {
+        hipLaunchKernelGGL((mfma_gemm_kernel<BITS, false, MS, false>), grid, dim3(256), 0, s, p, L.wfmt, nt, mt, plan.order);
+    }
 }
 
-int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, float *S, void *stream) {
+int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, void *Sv, float *tok, void *stream) {
     hipStream_t s = (hipStream_t)stream;
     const int64_t waves = (L.K + 2047) / 2048;
     const int threads = (int)(waves < 4 ? 64 * waves : 256);
+    if (L.act == LUTGEMM_ACT_INT8) {
+        const int64_t KP = (L.K + 255) / 256 * 256;
+        if (p.act) hipLaunchKernelGGL(prep_i8_kernel<false>, dim3((unsigned)p.M), dim3(threads), 0, s, p.act, (uint4 *)dst, (int *)Sv, tok, L.K, KP);
+        else hipLaunchKernelGGL(prep_i8_kernel<true>, dim3((unsigned)p.M), dim3(threads), 0, s, p.T, (uint4 *)dst, (int *)Sv, tok, L.K, KP);
+        return (int)hipGetLastError();
+    }
+    float *S = (float *)Sv;
     const size_t shm = S ? (size_t)L.KB * 4 : 0;
     const int Q = (int)L.Q, kpg = (int)(L.G / KBLK);
     if (p.act) hipLaunchKernelGGL(prep_kernel<false>, dim3((unsigned)p.M), dim3(threads), shm, s, p.act, (uint4 *)dst, S, L.K, Q, kpg);

@@ -163,15 +163,17 @@ struct LutPlan {
                      // per XCD; g >= 2: per XCD, bands of g token tiles, tokens fastest in a band)
     size_t ws_bytes;
     size_t part_off;  // byte offset of the split partial sums in the workspace (counters at 0)
-    size_t prep_off, prep_s_off;  // matrix-core kernel: prepared activations and their group sums
+    size_t prep_off, prep_s_off, prep_t_off;  // matrix-core kernel: prepared activations, their group
+                                              // sums, token factors (INT8 activations)
 };
 
 // fused: the plan of lutgemm_mpgemm_fused (the multi-token kernel that builds its tables
 // from the activations keeps a K range within MTOK_FUSED_SMAX blocks for zero-point formats)
 LutPlan plan_lut(const Layout &L, int64_t M, bool fused = false);
 
-// The matrix-core plan of (problem, M), kind 4, or kind -1 where the lookup kernels are planned.
-LutPlan plan_mfma(const Layout &L, int64_t M);
+// The matrix-core plan of (problem, M), kind 4, or kind -1 where the lookup kernels are planned;
+// fused: from the activations (lutgemm_mpgemm_fused), else from tables.
+LutPlan plan_mfma(const Layout &L, int64_t M, bool fused);
 
 // Smallest workspace lutgemm_mpgemm accepts for a valid problem: that of the lookup kernels.
 size_t min_workspace(const lutgemm_problem_t *problem, int64_t M);
@@ -264,8 +266,9 @@ int launch_mtok(const LutParams &p, const Layout &L, const LutPlan &plan, void *
 // The multi-token kernel building its tables from the FP16 activations (p.act).
 int launch_mtok_fused(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
 // Matrix-core path: the activations in operand order, from p.act or (NULL) the half tables
-// p.T, with their group sums if S != NULL; then the product (p.act = the prepared ones).
-int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, float *S, void *stream);
+// p.T, with their group sums if S != NULL (and, INT8 from p.act, the token factors); then the
+// product (p.act = the prepared ones).
+int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, void *S, float *tok, void *stream);
 int launch_mfma(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
 int launch_tri(const LutParams &p, const Layout &L, bool fused, void *stream);
 int launch_dequant(const DequantParams &p, const Layout &L, const DequantPlan &plan, void *stream);

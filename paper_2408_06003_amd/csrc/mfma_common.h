@@ -9,6 +9,8 @@ namespace lutgemm {
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef int intx4_t __attribute__((ext_vector_type(4)));
+typedef int intx16_t __attribute__((ext_vector_type(16)));
 
 // Chunk t (8 halves) of a 32-activation word in the MFMA order: activations 4 t + e (low
 // halves) and 4 t + e + 16 (high halves), e = 0..3.  x: the word's 32 halves in order.
@@ -100,6 +102,24 @@ __device__ __forceinline__ void mfma_decode(const uint2 (&w)[BITS], half8_t (&b)
             }
         }
     }
+}
+
+// The INT8 counterpart, one word: bit s + 8 i of the word (its b-bit field, value q) becomes
+// byte i of register s, s = 0..7; two fragments of 4 registers (K step 32 of the INT8 MFMA).
+template <int BITS>
+__device__ __forceinline__ void mfma_decode_i8(const uint32_t (&w)[BITS], intx4_t (&b)[2]) {
+    static_assert(BITS == 1 || BITS == 2, "binary or ternary planes");
+    uint32_t u[BITS];
+    if constexpr (BITS == 1) {
+        u[0] = undo_neg(w[0]);
+    } else {
+        const uint32_t y0 = undo_neg(w[0]), y1 = undo_neg(w[1]);
+        u[0] = bfi(0x55555555u, y0, y1 << 1);
+        u[1] = bfi(0x55555555u, y0 >> 1, y1);
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+        b[s >> 2][s & 3] = (int)(BITS == 1 ? (u[0] >> s) & 0x01010101u : (u[(s & 1) & (BITS - 1)] >> (s & ~1)) & 0x03030303u);
 }
 
 // w = sc (v - zo) for the decoded FP16 value v.

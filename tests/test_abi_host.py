@@ -298,8 +298,8 @@ def test_matrix_core_plan():
     for M in (16, 100, 4096):
         assert L.fused_workspace_size(p, M) >= L.workspace_size(p, M)
     i8 = L.problem(4096, 4096, 2, L.WFMT_TERNARY, 0, L.ACT_INT8, True)
+    assert L.workspace_size(i8, 4096) >= L.WORKSPACE_ZERO_BYTES + 4096 * 4096
     q8 = L.problem(4096, 4096, 2, L.WFMT_UINT, 128, L.ACT_FP16_LUT8)
-    for other in (i8, q8):
-        with tuning(MFMA=0):
-            ws = L.workspace_size(other, 4096)
-        assert L.workspace_size(other, 4096) == ws
+    with tuning(MFMA=0):
+        ws = L.workspace_size(q8, 4096)
+    assert L.workspace_size(q8, 4096) == ws

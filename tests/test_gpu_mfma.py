@@ -55,6 +55,51 @@ def test_formats_tiles_splits(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
     assert_fp_close(gp.lut(out_dtype=torch.float32).cpu().numpy(), ref, what + " table-fed")
 
 
+INT_CASES = [
+    (W.WFMT_TERNARY, 2, 0, True, 70, 1152, 300),      # 9 blocks: half of the last step is padding
+    (W.WFMT_TERNARY, 2, 640, False, 33, 640, 255),    # per channel
+    (W.WFMT_TERNARY, 2, 0, True, 3, 128, 1),          # one block, one column
+    (W.WFMT_BINARY, 1, 2944, False, 129, 2944, 513),  # 23 blocks
+    (W.WFMT_BINARY, 1, 0, True, 5, 256, 256),
+]
+
+
+@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("wfmt,bits,G,fp32,M,K,N", INT_CASES)
+def test_int8_bit_exact(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
+    tune(MFMA=1, MFMA_TILE=tile, MFMA_SPLITS=splits)
+    what = f"INT8 wfmt={wfmt} G={G} M={M} K={K} N={N} tile={tile} splits={splits}"
+    print(f"\n[case] {what}", flush=True)
+    inp = W.make_custom(wfmt, bits, G, W.ACT_INT8, M=M, K=K, N=N, seed=M + K + N, scale_fp32=fp32)
+    inp.act[1] = 0                       # a zero token
+    inp.act[2] *= np.float16(300)
+    gp = GpuProblem(inp)
+    acc_ref, y_ref = oracle.reference_output(inp)
+    for run in (gp.lut, gp.fused):
+        yi = run(out_dtype=torch.int32)
+        assert np.array_equal(yi.cpu().numpy().astype(np.int64), acc_ref), what
+        assert np.array_equal(run(out_dtype=torch.float32).cpu().numpy(), y_ref), what
+        base = torch.randint(-1000, 1000, (M, N), device="cuda", dtype=torch.int32)
+        acc = base.clone()
+        run(out=acc, accumulate=True)
+        assert torch.equal(acc, base + yi), what
+
+
+def test_int8_non_finite_activations(tune):
+    """Infinite and NaN activations give what the lookup kernels give for them."""
+    print("\n[case] INT8, inf and NaN activations", flush=True)
+    inp = W.make_custom(W.WFMT_TERNARY, 2, 0, W.ACT_INT8, M=20, K=512, N=300, seed=80, scale_fp32=True)
+    inp.act[3, 7] = np.float16(np.inf)
+    inp.act[4, 100] = np.float16(np.nan)
+    gp = GpuProblem(inp)
+    tune(MFMA=0)
+    ref = [run(out_dtype=torch.int32) for run in (gp.lut, gp.fused)]
+    tune(MFMA=1)
+    for run, r in zip((gp.lut, gp.fused), ref):
+        assert torch.equal(run(out_dtype=torch.int32), r)
+
+
 @pytest.mark.parametrize("splits", [1, 4])
 def test_tokens_and_accumulate(splits, tune):
     """Tokens of very different magnitude (FP16 subnormals, a zero token, large ones) each to
