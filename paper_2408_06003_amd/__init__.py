@@ -19,7 +19,7 @@ from typing import Optional
 # Load PyTorch's HIP runtime before the library: liblutgemm.so needs
 # libamdhip64.so.7, and the dynamic loader then binds it to the runtime already
 # in the process, so torch's streams and allocations are valid in our calls.
-import torch  # noqa: F401
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblutgemm.so")
@@ -146,8 +146,11 @@ def _ptr(x) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        # the raw handle of torch.cuda.current_stream(), without building a Stream object
+        # (0.1 us against 3.2 us, as much as a kernel launch)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
