@@ -44,7 +44,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic.txt")
 # sources that define each timed kernel and its launch (a PMC traffic record is used
 # only while they hash as when the counters were taken)
 KERNEL_SOURCES = {
-    "mpgemm": ("lut_gemv.hip", "lut_mtok.hip", "lut_mpgemm.hip", "lut_common.h", "lutgemm_internal.h", "api.cpp"),
+    "mpgemm": ("lut_gemv.hip", "lut_mtok.hip", "lut_mfma.hip", "mfma_few.hip", "mfma_common.h", "lut_mpgemm.hip", "lut_common.h", "lutgemm_internal.h", "api.cpp"),
     "fused": ("lut_fused.hip", "lut_mpgemm.hip", "lut_common.h", "lutgemm_internal.h", "api.cpp"),
     "dequant": ("dequant_mfma.hip", "lutgemm_internal.h", "api.cpp"),
 }

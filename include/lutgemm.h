@@ -231,13 +231,14 @@ lutgemm_status_t lutgemm_precompute(const lutgemm_problem_t *problem, int64_t M,
  *   workspace  device, workspace_bytes >= lutgemm_workspace_size(problem, M);
  *              may be NULL when that size is 0
  * FP path: O = t_m sum_q s'_q (sum_b 2^b sum_j L_{b,j} - z'_q S_q), FP32.
- * With several tokens (ACT_INT8: M >= 5.  ACT_FP16; UINT weights with group scales: M >= 16 and M N <= 2^24;
- * other UINT weights of 2 or 4 bits: 16 <= M <= 64, or M >= 16 and M N <= 2^20; other
- * weights: 16 <= M <= 32) the sums of lookups are evaluated on the matrix cores: an entry
- * is a signed sum of its 4 activations (Eq. 5), so the lookups of a column add up to the
- * dot product of its codes with the activations, which are recovered from the tables
- * (ACT_INT8: exactly, so the result is the same).  The tables must be half tables as the
- * layout defines.
+ * With several tokens (ACT_INT8: M >= 5.  ACT_FP16: from 5, 9 or 16 tokens on by K N, and
+ * for UINT weights with group scales M N <= 2^24; other UINT weights of 2 or 4 bits M <= 64
+ * or M N <= 2^20; other weights M <= 32) the sums of lookups are evaluated on the matrix
+ * cores: an entry is a signed sum of its 4 activations (Eq. 5), so the lookups of a column
+ * add up to the dot product of its codes with the activations, which are recovered from the
+ * tables (ACT_INT8: exactly, so the result is the same).  The tables must be half tables as
+ * the layout defines.  A token with a non-finite table entry gets non-finite outputs (NaN
+ * where the lookups may give an infinity).
  * INT8 path: acc = sum_k q_a w exactly; O = acc (INT32) or (float(acc) s_a) s_w.
  * TERNARY_3IN5: O = t_m s (sum_j L_j) (FP path, FP32) with one lookup per triple.
  * The result is bitwise reproducible run to run.
@@ -403,7 +404,7 @@ enum {
                                        cores: 0 never (the lookup kernels), 1 always (-1: planned;
                                        also off while a key of the multi-token lookup kernel, MT_* or
                                        MT4 / MT16, is away from its default)                        */
-    LUTGEMM_TUNE_MFMA_TILE = 18,    /* LUTGEMM_MFMA_TILE: tokens per workgroup there, 32, 64 or 128
+    LUTGEMM_TUNE_MFMA_TILE = 18,    /* LUTGEMM_MFMA_TILE: tokens per workgroup there, 16 (FP16 only), 32, 64 or 128
                                        (0: planned)                                                  */
     LUTGEMM_TUNE_MFMA_SPLITS = 19,  /* LUTGEMM_MFMA_SPLITS: K splits there (0: planned)              */
     LUTGEMM_TUNE_COUNT = 20

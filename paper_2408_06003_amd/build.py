@@ -26,7 +26,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblutgemm.so")
 TIMELINE_LIB = os.path.join(HERE, "liblutgemm_timeline.so")
-SOURCES = ["api.cpp", "pack.hip", "precompute.hip", "lut_gemv.hip", "lut_mpgemm.hip", "lut_fused.hip", "lut_mtok.hip", "lut_mfma.hip", "lut_tri.hip", "dequant_mfma.hip", "calib.hip", "noalloc.hip"]
+SOURCES = ["api.cpp", "pack.hip", "precompute.hip", "lut_gemv.hip", "lut_mpgemm.hip", "lut_fused.hip", "lut_mtok.hip", "lut_mfma.hip", "mfma_few.hip", "lut_tri.hip", "dequant_mfma.hip", "calib.hip", "noalloc.hip"]
 ARCH = "gfx950"
 
 COMMON = [

@@ -329,10 +329,17 @@ LutPlan plan_lut(const Layout &L, int64_t M, bool fused) {
 // Which calls go to the matrix cores.  INT8 activations (exact, so the same bits): from 3
 // tokens on where the activations are given, from 5 on from tables (graph replays, us,
 // lookups -> matrix cores: ternary 4096 x 4096 fused 12.5 -> 10.5 at M = 3, 29.3 -> 15.3 at
-// 64, 375 -> 64 at 2048; from tables 12.1 -> 13.1 at 3, 15.1 -> 13.8 at 5).  FP16 activations
-// win from 16 tokens on (INT4 4096 x 4096 18.5 -> 14.0 at M = 16, 112 -> 35 at 256, 679 ->
-// 100 at 2048; at 8 tokens three launches against two lose on small layers, 12.6 -> 13.5).
-// There they are also the more exact path, by so much that a call's result would move: the
+// 64, 375 -> 64 at 2048; from tables 12.1 -> 13.1 at 3, 15.1 -> 13.8 at 5).  FP16 activations:
+// the lookups take 8 tokens per pass and two launches where this path takes three, so the
+// line lies at 5, 9 or 16 tokens by what the larger or additional passes cost (graph replays,
+// us, lookups -> here, K x N): activations given, INT2 4096 x 4096 13.1 -> 11.4 at 5, binary
+// 1024 x 1024 13.2 -> 9.5; INT4 3072 x 8192 16.3 -> 14.1 at 5, 4096 x 4096 12.9 -> 13.5 at 8
+// and 16.7 -> 13.6 at 12, 1024 x 1024 12.2 -> 12.8 at 12 and 17.0 -> 12.8 at 16; from tables
+// (one more launch before the first product), 8192 x 28672 binary 26.8 -> 24.3 and INT2 37.6
+// -> 28.6 at 5; INT4 4096 x 12288 21.8 -> 21.0 at 5; INT2 6144 x 8192 17.0 -> 17.7 at 5 and
+// 21.9 -> 17.5 at 9, 4096 x 4096 14.4 -> 15.5 at 12 and 21.5 -> 15.9 at 16; INT4 there 19.5
+// -> 18.1 at 12; one bit in groups 3072 x 8192 15.6 -> 16.3 at 9, binary 15.2 -> 14.6.
+// The matrix cores are also the more exact path, by so much that a call's result would move: the
 // lookup kernel's FP16 word sums are off by 4.6-7.6e-4 (relative), and over many outputs with
 // one scale per column or tensor, where no group scales average them, its largest deviation
 // exceeds 1e-2 of the output's rms (24 seeds each, deviations over 1e-2: binary 8192 columns
@@ -342,7 +349,13 @@ LutPlan plan_lut(const Layout &L, int64_t M, bool fused) {
 // larger FP16 calls of those kinds stay with the lookups.
 static bool mfma_planned(const Layout &L, int64_t M, bool fused) {
     if (L.act == LUTGEMM_ACT_INT8) return M >= (fused ? 3 : 5);
-    if (M < 16) return false;
+    const int64_t MI = (int64_t)1 << 20, size = L.K * L.N;
+    int from;
+    if (size >= 40 * MI) from = fused || L.bits == 4 || size >= 128 * MI ? 5 : 9;
+    else if (fused) from = L.bits < 4 || size >= 20 * MI ? 5 : size >= 12 * MI ? 9 : 16;
+    else if (L.bits == 4) from = size >= 12 * MI ? 9 : 16;
+    else from = size >= 28 * MI || (L.bits == 1 && L.Q == 1) ? 9 : 16;
+    if (M < from) return false;
     if (L.wfmt == LUTGEMM_WFMT_UINT && L.Q > 1) return M * L.N <= (int64_t)1 << 24;
     if (L.bits > 1 && L.wfmt == LUTGEMM_WFMT_UINT) return M <= 64 || M * L.N <= (int64_t)1 << 20;
     return M <= 32;
@@ -356,6 +369,13 @@ static bool mfma_planned(const Layout &L, int64_t M, bool fused) {
 // (INT2 per channel 2432 x 11973 31 / 37 / 37 at 256, 64 / 60 / 69 at 700, 145 / 124 / 119 at
 // 2048); INT8 never 128 (110 / 108 / 131 there).  K is split to two workgroups per CU, at
 // least 4 blocks each.
+// Up to 16 FP16 tokens on a large layer go to the FP4 kernel (16 tokens x 256 columns, no
+// staged conversion; at least 8 blocks per range).  Its tile 32 rival decodes to FP16, which
+// takes three times the instructions, and multiplies 16 tokens of padding, but has the
+// cheaper first launch (us, 32 -> FP4 at M = 16: INT2 4096 x 8192 13.6 -> 13.3, at M = 5 12.3
+// -> 12.8; 6144 x 8192 16.4 -> 13.6; binary 8192 x 28672 25.9 -> 21.4; INT4 4096 x 8192 15.8
+// -> 17.1, 4096 x 12288 19.5 -> 17.6, 28672 x 8192 40.4 -> 42.0, where the decode of 4 bits
+// hides behind the weight stream either way).
 LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     LutPlan P{};
     P.kind = -1;
@@ -378,19 +398,30 @@ LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     if (M <= 32) P.mt = 32;
     const int tile = tuning(LUTGEMM_TUNE_MFMA_TILE);
     if (tile == 32 || tile == 64 || tile == 128) P.mt = tile;
+    const int64_t MI = (int64_t)1 << 20, size = L.K * L.N;
+    P.few = !i8 && M <= 16 && (tile == 16 || (tile == 0 && size >= 40 * MI && (L.bits < 4 || size < 128 * MI)));
+    if (P.few) P.mt = 16;
     P.m_tiles = (M + P.mt - 1) / P.mt;
     const int64_t base = P.n_tiles * P.m_tiles, target = 2 * tuning(LUTGEMM_TUNE_TARGET_BLOCKS);
     int64_t splits = base < target ? target / base : 1;
-    const int64_t max_splits = L.KB / 4 > 1 ? L.KB / 4 : 1;
+    const int64_t min_kbs = P.few ? 8 : 4, max_splits = L.KB / min_kbs > 1 ? L.KB / min_kbs : 1;
     if (splits > max_splits) splits = max_splits;
     const int fs = tuning(LUTGEMM_TUNE_MFMA_SPLITS);
     if (fs > 0) splits = fs < L.KB ? fs : L.KB;
     P.kbs = (int)((L.KB + splits - 1) / splits);
-    if (i8 && (P.kbs & 1)) ++P.kbs;  // whole steps of two blocks
+    if (P.few) {  // whole passes of the kernel
+        P.kbs = (P.kbs + 7) / 8 * 8;
+    } else if (i8 && (P.kbs & 1)) {
+        ++P.kbs;  // whole steps of two blocks
+    }
     P.splits = (int)((L.KB + P.kbs - 1) / P.kbs);
     P.order = 8;
     P.part_off = CNT_AREA;
     P.prep_off = CNT_AREA + (P.splits > 1 ? align256((size_t)P.splits * P.m_tiles * P.mt * L.N_pad * 4) : 0);
+    if (P.few) {
+        P.ws_bytes = P.prep_off + align256((size_t)mfma_few_prep_bytes(L));
+        return P;
+    }
     P.prep_s_off = P.prep_off + (i8 ? (size_t)P.m_tiles * P.mt * align256((size_t)L.K)  // whole token tiles
                                     : align256((size_t)P.m_tiles * P.mt * L.K * 2));
     P.prep_t_off = P.prep_s_off + align256((size_t)M * L.Q * 4);
@@ -450,6 +481,14 @@ static lutgemm_status_t run_mfma(const Layout &L, const LutPlan &plan, int64_t M
     LutParams lp = lut_params(L, plan, M, tables, packed, out, out_dtype, accumulate, workspace);
     lp.act = (const uint16_t *)act;
     const bool i8 = L.act == LUTGEMM_ACT_INT8;
+    if (plan.few) {
+        lp.act = (const uint16_t *)act;
+        int e = launch_mfma_few_prep(lp, L, ws + plan.prep_off, stream);
+        lp.act = (const uint16_t *)(ws + plan.prep_off);
+        if (e == 0) e = launch_mfma_few(lp, L, plan, stream);
+        if (e == 0 && plan.splits > 1) e = launch_finalize(lp, L, plan, stream);
+        return hip_error(e);
+    }
     void *S = i8 || L.wfmt != LUTGEMM_WFMT_BINARY ? ws + plan.prep_s_off : nullptr;
     float *tok = i8 && act ? (float *)(ws + plan.prep_t_off) : nullptr;
     int e = launch_mfma_prep(lp, L, ws + plan.prep_off, S, tok, stream);

@@ -74,6 +74,13 @@ __device__ __forceinline__ uint4 buf_u128(__amdgpu_buffer_rsrc_t r, uint32_t vof
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// (nontemporal: a read that should not displace cached data)
+__device__ __forceinline__ uint4 buf_u128_nt(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 2));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // Keeps a value in a VGPR so that loads indexed by it stay vector loads (scalar
 // loads share the LDS completion counter and would serialize the lookups).
 __device__ __forceinline__ int64_t lane_value(int64_t x) {
@@ -167,6 +174,16 @@ __device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) {
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t,
                               __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// Sum of v over each row of 16 lanes by DPP (quad_perm [1,0,3,2], [2,3,0,1], row half
+// mirror, row mirror): every lane of the row ends with the same bits.
+__device__ __forceinline__ float row_sum16(float v) {
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
+    return v;
 }
 
 // Maximum over the 64 lanes of an unsigned value (FP16 magnitude bits compare as

@@ -132,12 +132,11 @@ __global__ __launch_bounds__(256) void prep_i8_kernel(const void *src, uint4 *ds
                 const uint4 *T = (const uint4 *)src + m * (K / 4) + 8 * w;
 #pragma unroll
                 for (int g = 0; g < 8; ++g) {
-                    const uint4 e = T[g];
-                    const int t0 = (int16_t)(e.x & 0xFFFFu), t1 = (int)e.x >> 16, t2 = (int16_t)(e.y & 0xFFFFu), t4 = (int16_t)(e.z & 0xFFFFu);
-                    x[4 * g + 3] = (t1 - t0) >> 1;
-                    x[4 * g + 2] = (t2 - t0) >> 1;
-                    x[4 * g + 1] = (t4 - t0) >> 1;
-                    x[4 * g] = -t0 - x[4 * g + 1] - x[4 * g + 2] - x[4 * g + 3];
+                    const int4 q = table_acts_i8(T[g]);
+                    x[4 * g] = q.x;
+                    x[4 * g + 1] = q.y;
+                    x[4 * g + 2] = q.z;
+                    x[4 * g + 3] = q.w;
                 }
             } else {
 #pragma unroll

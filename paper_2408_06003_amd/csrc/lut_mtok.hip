@@ -57,16 +57,6 @@ __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel)
     return __builtin_amdgcn_perm(hi, lo, sel);
 }
 
-// Sum of v over each row of 16 lanes by DPP (quad_perm [1,0,3,2], [2,3,0,1], row half
-// mirror, row mirror): every lane of the row ends with the same bits.
-__device__ __forceinline__ float row_sum16(float v) {
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
-    return v;
-}
-
 template <bool INT8>
 __device__ __forceinline__ uint32_t neg16x2(uint32_t x) {
     if constexpr (INT8) return neg_i16x2(x);

@@ -161,6 +161,7 @@ struct LutPlan {
     int64_t n_tiles; // column tiles
     int order;       // multi-token kernel: workgroup order (0: columns fastest; 1: tokens fastest
                      // per XCD; g >= 2: per XCD, bands of g token tiles, tokens fastest in a band)
+    bool few;        // matrix cores: the few-token kernel (mfma_few.hip)
     size_t ws_bytes;
     size_t part_off;  // byte offset of the split partial sums in the workspace (counters at 0)
     size_t prep_off, prep_s_off, prep_t_off;  // matrix-core kernel: prepared activations, their group
@@ -270,6 +271,10 @@ int launch_mtok_fused(const LutParams &p, const Layout &L, const LutPlan &plan, 
 // product (p.act = the prepared ones).
 int launch_mfma_prep(const LutParams &p, const Layout &L, void *dst, void *S, float *tok, void *stream);
 int launch_mfma(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
+// The same for at most 16 FP16 tokens (mfma_few.hip).
+int64_t mfma_few_prep_bytes(const Layout &L);
+int launch_mfma_few_prep(const LutParams &p, const Layout &L, void *dst, void *stream);
+int launch_mfma_few(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream);
 int launch_tri(const LutParams &p, const Layout &L, bool fused, void *stream);
 int launch_dequant(const DequantParams &p, const Layout &L, const DequantPlan &plan, void *stream);
 

@@ -38,6 +38,13 @@ __device__ __forceinline__ uint2 table_acts(uint4 e) {
     return make_uint2(pack(x0, x1), pack(x2, x3));
 }
 
+// The four INT8 activations behind a half table of INT16 entries, exactly.
+__device__ __forceinline__ int4 table_acts_i8(uint4 e) {
+    const int t0 = (int16_t)(e.x & 0xFFFFu), t1 = (int)e.x >> 16, t2 = (int16_t)(e.y & 0xFFFFu), t4 = (int16_t)(e.z & 0xFFFFu);
+    const int x3 = (t1 - t0) >> 1, x2 = (t2 - t0) >> 1, x1 = (t4 - t0) >> 1;
+    return make_int4(-t0 - x1 - x2 - x3, x1, x2, x3);
+}
+
 // Low 3 bits of every 4-bit index inverted where its bit 3 is set: undoes the offline
 // negation of Eq. 6 for 8 indices at once (8 - 1 = 7 per set sign bit).
 __device__ __forceinline__ uint32_t undo_neg(uint32_t w) {
@@ -160,11 +167,6 @@ __device__ __forceinline__ bf16x8_t split3_b(float x) {
     const Split3 s = split3(x);
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(bf16x8_t, (u32x4){s.h | (s.m << 16), s.h | (s.l << 16), s.h | (s.m << 16), s.l | (s.m << 16)});
-}
-
-// Quantization group of 128-block kb (workgroup-uniform).
-__device__ __forceinline__ int kb_group(const LutParams &p, int kb) {
-    return __builtin_amdgcn_readfirstlane((int)(((float)kb + 0.5f) * p.inv_kpg));
 }
 
 struct MTile {

@@ -1,0 +1,355 @@
+// Up to 16 tokens on the matrix cores: the product of lut_mfma.hip with the weights as FP4.
+//
+// At a few tokens the call is one stream of packed weights, and decoding them into FP16
+// operands costs more than reading them (36 vector instructions per 32 one-bit weights, 84
+// per 32 four-bit ones).  v_mfma_scale_f32_16x16x128_f8f6f4 takes its operands in different
+// formats, so the weights stay in 4 bits, which is how the planes hold them: a 32-bit plane
+// word is 8 nibbles (the 8 groups of 4 weights), so one shift brings bit e of every nibble to
+// the sign position of an FP4 value, and 8 weights are decoded at a time (11 instructions per
+// 32 one-bit weights: +-1; 25 per 32 two-bit ones: the reinterpreted code of Eq. 2, {-3, -1,
+// 1, 3} as +-0.5, +-1.5; 4 bits: two such halves, the upper one scaled by 4).
+//
+// The activations become three FP8 terms each, exactly: with the 32 activations of a word
+// scaled by a power of two so that the largest lies in [128, 256) (the E8M0 scale of the
+// instruction), t1 = fp8(x), t2 = fp8(16 (x - t1)), t3 = fp8(16 (16 (x - t1) - t2)) reproduce
+// the 11 significant bits of an FP16 value down to 2^-14 of the word's largest, below which
+// 2^-26 of it is lost.  prep_few_kernel writes them once per call in operand order.
+//
+// The k order: slot 32 g + 8 e + i of a 128-block's 128 is weight 4 i + e of word g.  Lane (c, g)
+// = (lane % 16, lane / 16) of the FP4 operand holds slots 32 g .. + 31, so its register e is bit
+// 3 - e of the 8 nibbles of column c's word g, and its scale byte is that of these slots; the
+// FP8 operand holds slots 16 g .. + 15 in registers 0..3 and 64 + 16 g .. + 15 in 4..7.
+//
+// Bound by instruction issue at 1 bit and by the weight stream at 4: a workgroup of 4 wavefronts
+// takes 256 columns (64 per wavefront, four independent chains of products), 8 / b blocks of
+// weight words per wavefront in flight, the activations through two LDS buffers.  16 x 8192 x
+// 28672, product alone: binary 17.8 us (FP16 tiles of lut_mfma.hip 22), 4 bits in groups 35.3;
+// whole call, before by lookups -> now: binary 40.7 -> 21.5, INT2 60.0 -> 26.2, INT4 4096 x
+// 12288 32.8 -> 17.6.  512 columns per workgroup (8 wavefronts, half the activation reads) ran
+// 18.4 and 18.8 where this took 17.8 and 13.5 (INT4 8 x 4096 x 12288); the whole K range of
+// activations resident in LDS (one barrier, one workgroup per CU) 24.7 against 21.5 per call.
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+
+#include "lut_common.h"
+#include "mfma_common.h"
+
+namespace lutgemm {
+
+typedef int intx8_t __attribute__((ext_vector_type(8)));
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void;
+
+// One prepared 128-block of 16 tokens: 3 terms x 2 halves x 64 lanes x 16 bytes, 64 dwords of
+// scales (bytes 0..2: the terms' E8M0 exponents), 16 activation sums (FP32), padded to 7 KiB.
+constexpr int FEW_TERM = 2048, FEW_SCALE = 6144, FEW_SUM = 6400, FEW_BLK = 7168;
+constexpr int FEW_CB = 4;           // blocks per LDS buffer, one per wavefront of its load
+constexpr int FEW_U = 2 * FEW_CB;   // blocks per pass: both buffers once
+
+// One 128-block per wavefront: lane (r, g) = token r, word g.  Tokens past M and blocks past K
+// are zero.  TAB: from half tables (see prep_kernel).
+template <bool TAB>
+__global__ __launch_bounds__(64) void prep_few_kernel(const void *src, char *dst, int64_t M, int64_t K) {
+    const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+    const int64_t kb = blockIdx.x;
+    uint2 h[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = make_uint2(0u, 0u);
+    if (r < M && kb * KBLK < K) {
+        if constexpr (TAB) {
+            const uint4 *T = (const uint4 *)src + r * (K / 4) + kb * GPB + 8 * g;
+            uint4 e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = T[i];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) h[i] = table_acts(e[i]);
+        } else {
+            const uint4 *a = (const uint4 *)((const uint16_t *)src + r * K + kb * KBLK + 32 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint4 v = a[i];
+                h[2 * i] = make_uint2(v.x, v.y);
+                h[2 * i + 1] = make_uint2(v.z, v.w);
+            }
+        }
+    }
+    uint32_t mx = 0u;
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        mx = max_u16x2(mx, max_u16x2(h[i].x & 0x7FFF7FFFu, h[i].y & 0x7FFF7FFFu));
+        sum = (((sum + h2f(h[i].x & 0xFFFFu)) + h2f(h[i].x >> 16)) + h2f(h[i].y & 0xFFFFu)) + h2f(h[i].y >> 16);
+    }
+    const uint32_t m16 = (mx & 0xFFFFu) > (mx >> 16) ? (mx & 0xFFFFu) : (mx >> 16);
+    int e2 = 8;
+    if (m16 != 0u && m16 < 0x7C00u) (void)frexpf(h2f(m16), &e2);  // largest = f 2^e2, f in [0.5, 1)
+    const int s = e2 - 8;
+    // an infinity or NaN makes the word's products NaN (E8M0 has that value, FP8 no infinity)
+    const uint32_t sb = m16 >= 0x7C00u ? 0x00FFFFFFu : (uint32_t)(s + 127) | (uint32_t)(s + 123) << 8 | (uint32_t)(s + 119) << 16;
+    uint32_t t[3][8];
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {  // slots 4 d .. 4 d + 3: e = d / 2, groups i = 4 (d % 2) ..
+        float x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint2 v = h[4 * (d & 1) + k];
+            const uint32_t w = (d >> 2) ? v.y : v.x;
+            x[k] = m16 >= 0x7C00u ? 0.f : ldexpf(h2f(((d >> 1) & 1) ? w >> 16 : w & 0xFFFFu), -s);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            int w = __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], 0, false);
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(x[2], x[3], w, true);
+            t[j][d] = (uint32_t)w;
+            x[0] = 16.f * (x[0] - __builtin_amdgcn_cvt_f32_fp8(w, 0));
+            x[1] = 16.f * (x[1] - __builtin_amdgcn_cvt_f32_fp8(w, 1));
+            x[2] = 16.f * (x[2] - __builtin_amdgcn_cvt_f32_fp8(w, 2));
+            x[3] = 16.f * (x[3] - __builtin_amdgcn_cvt_f32_fp8(w, 3));
+        }
+    }
+    char *d = dst + kb * FEW_BLK;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const int q = 2 * g + hf;  // which 16 of the block's 128 slots
+            *(uint4 *)(d + j * FEW_TERM + (q >> 2) * 1024 + ((q & 3) * 16 + r) * 16) =
+                make_uint4(t[j][4 * hf], t[j][4 * hf + 1], t[j][4 * hf + 2], t[j][4 * hf + 3]);
+        }
+    *(uint32_t *)(d + FEW_SCALE + 4 * lane) = sb;
+    sum = xor_sum_f<32>(xor_sum_f<16>(sum));
+    if (lane < 16) *(float *)(d + FEW_SUM + 4 * lane) = sum;
+}
+
+// The FP4 operand of one part (one plane: +-1; two planes hi, lo: +-0.5, +-1.5) of the words
+// at lane (c, g).  y: Eq. 6 undone.
+__device__ __forceinline__ void fp4_one(uint32_t y, uint32_t (&r)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = (~(y << e) & 0x88888888u) | 0x22222222u;
+}
+__device__ __forceinline__ void fp4_two(uint32_t hi, uint32_t lo, uint32_t (&r)[4]) {
+    const uint32_t big = ~(hi ^ lo);  // |q'| = 3 where the bits agree
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t m = e < 2 ? big >> (2 - e) : big << (e - 2);
+        r[e] = (~(hi << e) & 0x88888888u) | ((m & 0x22222222u) | 0x11111111u);
+    }
+}
+
+template <int BITS, bool GRP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void mfma_few_kernel(LutParams p, int wfmt, uint32_t n_tiles) {
+    constexpr int D = 8 / BITS;                    // blocks of weight words in flight
+    constexpr int U = FEW_U;
+    constexpr int LPB = BITS + (GRP ? 4 : 0);      // loads per block (words, metadata)
+    __shared__ __attribute__((aligned(16))) char A0[FEW_CB * FEW_BLK], A1[FEW_CB * FEW_BLK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const uint32_t nt = blockIdx.x % n_tiles;
+    const int split = blockIdx.x / n_tiles;
+    const uint32_t n0 = nt * NTILE + wave * 64;  // the wavefront's columns
+    const int kbA = split * p.kbs;
+    const int nkb = (kbA + p.kbs < (int)p.KB ? kbA + p.kbs : (int)p.KB) - kbA;
+    const int npass = (nkb + U - 1) / U;         // (prepared blocks past K are zero)
+
+    // prepared blocks kb .. kb + 3 of the range into dst, one per wavefront
+    const __amdgpu_buffer_rsrc_t rA = buf_rsrc((const char *)p.act + (int64_t)kbA * FEW_BLK, (uint32_t)(npass * U + 2 * FEW_CB) * FEW_BLK);
+    auto load_act = [&](int kb, char *dst) {
+        const uint32_t so = (uint32_t)(kb + wave) * FEW_BLK;
+#pragma unroll
+        for (int i = 0; i < FEW_BLK / 1024; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void *)(dst + wave * FEW_BLK + 1024 * i), 16, 16 * lane, (int)(so + 1024u * i), 0, 0);
+    };
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    struct W {
+        u32x4 w[BITS];  // (whole vectors: a ring of scalars would be copied, and waited for, on arrival)
+        uint32_t m[4];
+    };
+    int q_cur = GRP ? kbA / p.kpg : 0;  // quantization group of the last block loaded
+    // the 64 columns' words of block kb, a column per lane, and the metadata of columns 16 cb +
+    // c (past the range: its last block again, against zero activations)
+    auto load_w = [&](int kb, W &w) {
+        const int kc = kbA + (kb < nkb ? kb : nkb - 1);
+        const __amdgpu_buffer_rsrc_t rW =
+            buf_rsrc(p.planes + (int64_t)kc * BITS * p.N_pad, (uint32_t)BITS * (uint32_t)p.N_pad * 16u);
+#pragma unroll
+        for (int t = 0; t < BITS; ++t)
+            w.w[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, (int)((n0 + lane) * 16u), (int)((uint32_t)t * (uint32_t)p.N_pad * 16u), 2));
+        if constexpr (GRP) {
+            if (kc >= (q_cur + 1) * p.kpg) ++q_cur;  // blocks are loaded in order
+            const __amdgpu_buffer_rsrc_t rM = buf_rsrc((const uint32_t *)p.meta + (int64_t)q_cur * p.N_pad, (uint32_t)p.N_pad * 4u);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) w.m[cb] = buf_u32(rM, (n0 + 16 * cb + c) * 4u, 0);
+        }
+    };
+
+    floatx4_t acc[4], stot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) acc[cb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+
+    // the activation operands of a block, read from LDS one block ahead
+    struct A {
+        intx8_t a[3];
+        int sa;
+        floatx4_t S;  // sums of tokens 4 g .. 4 g + 3
+    };
+    auto read_act = [&](const char *as, A &x) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint4 lo = *(const uint4 *)(as + j * FEW_TERM + 16 * lane), hi = *(const uint4 *)(as + j * FEW_TERM + 1024 + 16 * lane);
+            x.a[j] = intx8_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+        }
+        x.sa = *(const int *)(as + FEW_SCALE + 4 * lane);
+        x.S = *(const floatx4_t *)(as + FEW_SUM + 16 * g);
+    };
+    auto block = [&](const A &x, W &w) {
+        if constexpr (!GRP) stot += x.S;
+        // word g of columns 16 cb + c at lane (c, g): a 4 x 4 transpose over the lane groups
+        uint32_t y[BITS][4];
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) {
+            const auto p02 = __builtin_amdgcn_permlane32_swap(w.w[t].x, w.w[t].z, false, false);
+            const auto p13 = __builtin_amdgcn_permlane32_swap(w.w[t].y, w.w[t].w, false, false);
+            const auto q01 = __builtin_amdgcn_permlane16_swap(p02[0], p13[0], false, false);
+            const auto q23 = __builtin_amdgcn_permlane16_swap(p02[1], p13[1], false, false);
+            y[t][0] = undo_neg(q01[0]);
+            y[t][1] = undo_neg(q01[1]);
+            y[t][2] = undo_neg(q23[0]);
+            y[t][3] = undo_neg(q23[1]);
+        }
+        floatx4_t tmp[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) tmp[cb] = GRP ? floatx4_t{0.f, 0.f, 0.f, 0.f} : acc[cb];
+#pragma unroll
+        for (int part = 0; part < (BITS == 4 ? 2 : 1); ++part) {
+            intx8_t b[4];
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                uint32_t r[4];
+                if constexpr (BITS == 1) fp4_one(y[0][cb], r);
+                else fp4_two(y[2 * part + 1][cb], y[2 * part][cb], r);
+                b[cb] = intx8_t{(int)r[0], (int)r[1], (int)r[2], (int)r[3], 0, 0, 0, 0};
+            }
+            // E8M0: 1 bit as it is; 2 bits times 2; the upper two of 4 times 8.  The four
+            // columns' chains alternate, so that no product waits for the one before it.
+            const int sbv = part ? 0x82 : (BITS == 1 ? 0x7F : 0x80);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) tmp[cb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x.a[0], b[cb], tmp[cb], 0, 4, 0, x.sa, 0, sbv);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) tmp[cb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x.a[1], b[cb], tmp[cb], 0, 4, 1, x.sa, 0, sbv);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) tmp[cb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x.a[2], b[cb], tmp[cb], 0, 4, 2, x.sa, 0, sbv);
+        }
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            if constexpr (GRP) {
+                const float sp = p.cs * h2f(w.m[cb] & 0xFFFFu), zp = fmaf(p.cz, h2f(w.m[cb] >> 16), p.c0);
+                const float nsz = -(sp * zp);  // (0 for binary weights)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[cb][v] = fmaf(sp, tmp[cb][v], fmaf(nsz, x.S[v], acc[cb][v]));
+            } else {
+                acc[cb] = tmp[cb];
+            }
+        }
+    };
+
+    // A buffer's blocks are in registers when its last block's turn comes; then the other
+    // buffer has to be there (waited for), and this one may be filled again.  Loads return in
+    // order, and at least three blocks of weight loads (LPB each) follow the request for a
+    // buffer: it has returned when at most two blocks' are in flight.
+    auto wait_act = [&]() {
+        constexpr int n = 2 * LPB;
+        static_assert(n < 64, "vmcnt");
+        __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | (7 << 4));  // vmcnt(n) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    W w[D];
+    A x[2];
+    load_act(0, A0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < D; ++u) load_w(u, w[u]);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_s_barrier();
+    load_act(FEW_CB, A1);
+    __builtin_amdgcn_sched_barrier(0);
+    read_act(A0, x[0]);
+    for (int kk = 0; kk < npass * U; kk += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u % FEW_CB == FEW_CB - 1) {
+                wait_act();
+                load_act(kk + u + 1 + FEW_CB, u < FEW_CB ? A0 : A1);  // (past the range: never used)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int un = (u + 1) % U;  // (after the last pass: a block that is not used)
+            read_act((un < FEW_CB ? A0 : A1) + (un % FEW_CB) * FEW_BLK, x[(u + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            block(x[u & 1], w[u % D]);
+            load_w(kk + u + D, w[u % D]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // no load into LDS outlives the workgroup
+
+    // lane: columns 16 cb + c, tokens 4 g + v
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+        const int64_t n = n0 + 16 * cb + c;
+        float sp = 1.f, nsz = 0.f;
+        if constexpr (!GRP) {
+            const SZ s = decode_sz(p, load_meta_words(p, 0, n));
+            sp = s.sp;
+            nsz = -(s.sp * s.zp);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t m = 4 * g + v;
+            if (m >= p.M) continue;
+            float y = acc[cb][v];
+            if constexpr (!GRP) {
+                y = fmaf(nsz, stot[v], y * sp);
+            }
+            if (p.splits > 1) {
+                p.part[((int64_t)split * 16 + m) * p.N_pad + n] = y;
+            } else if (n < p.N) {
+                const Epi ep = load_epi<false>(p, wfmt, m, n, false);
+                store_out<false>(p, wfmt, m, n, y, 0, ep);
+            }
+        }
+    }
+}
+
+int64_t mfma_few_prep_bytes(const Layout &L) {  // whole passes, and the two buffers past the last
+    return ((L.KB + 7) / 8 * 8 + 2 * FEW_CB) * FEW_BLK;
+}
+
+int launch_mfma_few_prep(const LutParams &p, const Layout &L, void *dst, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    const dim3 grid((unsigned)((L.KB + 7) / 8 * 8));
+    if (p.act) hipLaunchKernelGGL(prep_few_kernel<false>, grid, dim3(64), 0, s, p.act, (char *)dst, p.M, L.K);
+    else hipLaunchKernelGGL(prep_few_kernel<true>, grid, dim3(64), 0, s, p.T, (char *)dst, p.M, L.K);
+    return (int)hipGetLastError();
+}
+
+int launch_mfma_few(const LutParams &p, const Layout &L, const LutPlan &plan, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    const dim3 grid((unsigned)(plan.n_tiles * plan.splits));
+    const uint32_t nt = (uint32_t)plan.n_tiles;
+    const bool grp = L.Q > 1;
+    if (p.M > 16) return (int)hipErrorInvalidValue;
+    if (L.bits == 1) {
+        if (grp) hipLaunchKernelGGL((mfma_few_kernel<1, true>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+        else hipLaunchKernelGGL((mfma_few_kernel<1, false>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+    } else if (L.bits == 2) {
+        if (grp) hipLaunchKernelGGL((mfma_few_kernel<2, true>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+        else hipLaunchKernelGGL((mfma_few_kernel<2, false>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+    } else {
+        if (grp) hipLaunchKernelGGL((mfma_few_kernel<4, true>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+        else hipLaunchKernelGGL((mfma_few_kernel<4, false>), grid, dim3(256), 0, s, p, L.wfmt, nt);
+    }
+    return (int)hipGetLastError();
+}
+
+}  // namespace lutgemm

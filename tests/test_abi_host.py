@@ -284,7 +284,7 @@ def test_tuning_overrides():
 
 
 def test_matrix_core_plan():
-    """From 16 FP16 tokens on the workspace covers the matrix-core path (prepared activations
+    """From 5, 9 or 16 FP16 tokens on, by the layer's size, the workspace covers the matrix-core path (prepared activations
     of whole token tiles); an override of the lookup kernel's plan, or the key itself, takes
     the lookup kernels' size back."""
     p = L.problem(4096, 4096, 2, L.WFMT_UINT, 128)
@@ -293,6 +293,15 @@ def test_matrix_core_plan():
         small = L.workspace_size(p, 15)
     assert L.workspace_size(p, 4096) >= L.WORKSPACE_ZERO_BYTES + 4096 * 4096 * 2
     assert L.workspace_size(p, 15) == small
+    for K, N, bits, first in [(4096, 12288, 4, 5), (4096, 4096, 4, 9), (1024, 1024, 4, 16), (6144, 8192, 2, 9),
+                              (8192, 28672, 2, 5), (3072, 8192, 2, 16), (4096, 8192, 2, 9)]:
+        q = L.problem(K, N, bits, L.WFMT_UINT, 128)
+        for M in (first - 1, first):
+            planned = L.workspace_size(q, M)
+            with tuning(MFMA=0):
+                lookups = L.workspace_size(q, M)
+            with tuning(MFMA=1):
+                assert planned == (L.workspace_size(q, M) if M >= first else lookups)
     with tuning(MT_ORDER=1):
         assert L.workspace_size(p, 4096) == 0
     for M in (16, 100, 4096):

@@ -37,7 +37,7 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("tile", [16, 32, 64, 128])
 @pytest.mark.parametrize("splits", [1, 3])
 @pytest.mark.parametrize("wfmt,bits,G,fp32,M,K,N", CASES)
 def test_formats_tiles_splits(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
@@ -55,6 +55,68 @@ def test_formats_tiles_splits(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
     assert_fp_close(gp.lut(out_dtype=torch.float32).cpu().numpy(), ref, what + " table-fed")
 
 
+FEW_CASES = [
+    # at most 16 tokens: passes of 8 blocks, the last one partly past K or past the range
+    (W.WFMT_UINT, 4, 128, False, 16, 1152, 300),     # 9 blocks
+    (W.WFMT_UINT, 2, 512, False, 9, 2048, 257),      # groups of 4 blocks
+    (W.WFMT_UINT, 1, 128, False, 3, 128, 1),         # one block, one column
+    (W.WFMT_UINT, 1, 0, False, 15, 640, 255),
+    (W.WFMT_UINT, 4, 1280, False, 5, 1280, 513),
+    (W.WFMT_UINT, 2, 0, False, 16, 4096, 64),
+    (W.WFMT_BINARY, 1, 256, False, 7, 1536, 300),
+    (W.WFMT_BINARY, 1, 0, True, 16, 384, 256),
+    (W.WFMT_TERNARY, 2, 128, False, 4, 1024, 300),
+    (W.WFMT_TERNARY, 2, 0, True, 13, 2944, 100),     # 23 blocks
+]
+
+
+@pytest.mark.parametrize("splits", [1, 2, 3])
+@pytest.mark.parametrize("wfmt,bits,G,fp32,M,K,N", FEW_CASES)
+def test_few_tokens(wfmt, bits, G, fp32, M, K, N, splits, tune):
+    """FP4 weights and three FP8 activation terms, token by token, with tokens of very different
+    magnitude and activations spread over 2^12.  The operands are exact; the instruction aligns
+    its 128 products to the largest one and keeps about 14 bits below it, so what a spread of
+    2^12 costs is bounded by 2^-13 of the terms' magnitude (measured at most 6.4e-5; N(0, 1)
+    activations, in the other tests, 6e-6)."""
+    tune(MFMA=1, MFMA_TILE=16, MFMA_SPLITS=splits)
+    what = f"few tokens wfmt={wfmt} b={bits} G={G} M={M} K={K} N={N} splits={splits}"
+    print(f"\n[case] {what}", flush=True)
+    inp = W.make_custom(wfmt, bits, G, W.ACT_FP16, M=M, K=K, N=N, seed=2 * M + K + N, scale_fp32=fp32)
+    a = inp.act.astype(np.float32) * np.exp2(np.random.default_rng(7).integers(-10, 3, inp.act.shape))
+    a[0] *= 1e-4
+    a[1] = 0.0
+    a[2] *= 1e3
+    inp.act = a.astype(np.float16)
+    gp = GpuProblem(inp)
+    ref = oracle.reference_output(inp)
+    y = gp.fused(out_dtype=torch.float32)
+    yt = gp.lut(out_dtype=torch.float32)
+    for m in range(M):
+        if m == 1:
+            assert not y[m].any() and not yt[m].any()
+            continue
+        fro, _ = fp_errors(y[m].cpu().numpy(), ref[m])
+        assert fro <= 2.0 ** -13, f"{what}: token {m} relative error {fro:.3e}"
+        assert_fp_close(yt[m].cpu().numpy(), ref[m], f"{what} table-fed token {m}")
+    assert torch.equal(gp.fused(out_dtype=torch.float32), y), f"{what}: two runs differ bitwise"
+    assert torch.equal(gp.fused(out_dtype=torch.float16), y.half())
+
+
+@pytest.mark.parametrize("M", [4, 40])
+def test_non_finite_tokens(M, tune):
+    """An infinite or NaN activation makes its own token's outputs non-finite, no other's."""
+    tune(MFMA=1)
+    print(f"\n[case] non-finite activations M={M}", flush=True)
+    inp = W.make_custom(W.WFMT_UINT, 2, 128, W.ACT_FP16, M=M, K=1024, N=300, seed=81)
+    clean = oracle.reference_output(inp)
+    inp.act[1, 200] = np.float16(np.inf)
+    inp.act[2, 900] = np.float16(np.nan)
+    y = GpuProblem(inp).fused(out_dtype=torch.float32).cpu().numpy()
+    assert not np.isfinite(y[1]).any() and not np.isfinite(y[2]).any()
+    for m in [0] + list(range(3, M)):
+        assert fp_errors(y[m], clean[m])[0] <= 1e-5
+
+
 INT_CASES = [
     (W.WFMT_TERNARY, 2, 0, True, 70, 1152, 300),      # 9 blocks: half of the last step is padding
     (W.WFMT_TERNARY, 2, 640, False, 33, 640, 255),    # per channel
@@ -64,7 +126,7 @@ INT_CASES = [
 ]
 
 
-@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("tile", [16, 32, 64, 128])
 @pytest.mark.parametrize("splits", [1, 3])
 @pytest.mark.parametrize("wfmt,bits,G,fp32,M,K,N", INT_CASES)
 def test_int8_bit_exact(wfmt, bits, G, fp32, M, K, N, tile, splits, tune):
