@@ -361,14 +361,49 @@ static bool mfma_planned(const Layout &L, int64_t M, bool fused) {
     return M <= 32;
 }
 
-// Tile (tokens per workgroup) of the matrix-core plan: a larger one decodes each weight for
-// more tokens, a smaller one gives more workgroups and so fewer K splits.  With group scales
-// (the dearer decode) 128 tokens win from 96 such tiles on and 64 from 47 (INT4, tiles of
-// 32 / 64 / 128, us: 4096 x 4096 68 / 57 / 54 at M = 700, 25 / 25 / 29 at 100; 2432 x 11973
-// 31 / 29 / 30 at 100, 43 / 43 / 42 at 256); without, 64 from 512 tiles on and 128 from 700
-// (INT2 per channel 2432 x 11973 31 / 37 / 37 at 256, 64 / 60 / 69 at 700, 145 / 124 / 119 at
-// 2048); INT8 never 128 (110 / 108 / 131 there).  K is split to two workgroups per CU, at
-// least 4 blocks each.
+// Time of a matrix-core plan in us without what all plans of a call share: blocks per K range
+// times the time of one (a longer tile decodes each weight for more tokens; two workgroups on
+// a CU take 1.65 times as long as one, further ones wait their turn; INT8 tiles are small
+// enough to share it), the workgroups' start and
+// end, and with several ranges the partial sums written and read once and the launch that adds
+// them.  The constants are a least-squares fit (relative error 6 %) over tiles of 32, 64 and 128
+// tokens, 1-16 ranges, 17-2048 tokens, layers of 1024 x 1024 to 28672 x 8192 and INT4 and INT2 in
+// groups, INT2 and binary per channel and INT8 ternary.  Its choice is 1-2 % slower than the
+// best of those plans on average (at most 15 %), where rules by tile counts, split to two workgroups per CU,
+// were 5-10 % (us, rules -> here: INT4 256 x 4096 x 4096 35.9 -> 33.8, INT2 per channel 512 x
+// 28672 x 8192 294 -> 216, binary 512 x 4096 x 4096 41.2 -> 31.2, 2048 x 1024 x 1024 29.4 ->
+// 16.6; INT8 256 x 4096 x 4096 28.8 -> 24.1).
+static float mfma_cost(const Layout &L, int64_t M, int t, int splits, int cus) {
+    const bool i8 = L.act == LUTGEMM_ACT_INT8;
+    int kbs = (int)((L.KB + splits - 1) / splits);
+    if (i8 && (kbs & 1)) ++kbs;
+    const int S = (int)((L.KB + kbs - 1) / kbs);
+    const int64_t mt = (M + t - 1) / t, wgs = L.N_pad / NTILE * mt * S;
+    const int64_t r = (wgs + cus - 1) / cus;
+    const float rounds = (float)r, pairs = (float)((r + 1) / 2);
+    const float b = (float)L.bits, g = L.Q > 1 ? 1.f : 0.f;
+    float block, ends;
+    if (i8) {
+        block = (t == 32 ? 0.42f : 0.67f) * (1.f + (t == 32 ? 0.61f : 0.51f) * (rounds - 1.f));
+        ends = (t == 32 ? 0.f : 0.52f) + (S > 1 ? 0.f : 1.2f);
+    } else if (t == 32) {
+        block = 0.40f + 0.13f * b + 0.22f * g;
+        ends = 0.f;
+    } else if (t == 64) {
+        block = 0.70f + 0.15f * b + 0.25f * g;
+        ends = 0.45f * pairs;
+    } else {
+        block = 1.2f + 0.2f * b + 0.45f * g;
+        ends = 2.3f * pairs;
+    }
+    if (!i8 && rounds > 1.f) block *= 0.825f * (rounds > 2.f ? rounds : 2.f);
+    const float sums = S > 1 ? 1.2f + 0.118e-6f * 8.f * (float)S * (float)(mt * t) * (float)L.N_pad : 0.f;
+    return (float)kbs * block + ends + sums;
+}
+
+// Tile (tokens per workgroup) and K ranges (at least 3 blocks each) of the matrix-core plan: the
+// cheapest by mfma_cost.  INT8 never 128 (110 / 108 / 131 us with 32 / 64 / 128 at 2048 x 2432 x
+// 11973).
 // Up to 16 FP16 tokens on a large layer go to the FP4 kernel (16 tokens x 256 columns, no
 // staged conversion; at least 8 blocks per range).  Its tile 32 rival decodes to FP16, which
 // takes three times the instructions, and multiplies 16 tokens of padding, but has the
@@ -391,23 +426,37 @@ LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     }
     P.kind = 4;
     P.n_tiles = L.N_pad / NTILE;
-    auto tiles = [&](int mt) { return P.n_tiles * ((M + mt - 1) / mt); };
-    const bool grp = L.Q > 1;
-    P.mt = !i8 && tiles(128) >= (grp ? 96 : 700) ? 128 : tiles(64) >= (grp ? 47 : 512) ? 64 : 32;
-    if (M <= 64 && P.mt == 128) P.mt = 64;
-    if (M <= 32) P.mt = 32;
     const int tile = tuning(LUTGEMM_TUNE_MFMA_TILE);
-    if (tile == 32 || tile == 64 || tile == 128) P.mt = tile;
     const int64_t MI = (int64_t)1 << 20, size = L.K * L.N;
     P.few = !i8 && M <= 16 && (tile == 16 || (tile == 0 && size >= 40 * MI && (L.bits < 4 || size < 128 * MI)));
-    if (P.few) P.mt = 16;
-    P.m_tiles = (M + P.mt - 1) / P.mt;
-    const int64_t base = P.n_tiles * P.m_tiles, target = 2 * tuning(LUTGEMM_TUNE_TARGET_BLOCKS);
-    int64_t splits = base < target ? target / base : 1;
-    const int64_t min_kbs = P.few ? 8 : 4, max_splits = L.KB / min_kbs > 1 ? L.KB / min_kbs : 1;
-    if (splits > max_splits) splits = max_splits;
+    const int cus = tuning(LUTGEMM_TUNE_TARGET_BLOCKS) > 0 ? tuning(LUTGEMM_TUNE_TARGET_BLOCKS) : 256;
     const int fs = tuning(LUTGEMM_TUNE_MFMA_SPLITS);
-    if (fs > 0) splits = fs < L.KB ? fs : L.KB;
+    int64_t splits = fs > 0 ? (fs < L.KB ? fs : L.KB) : 1;
+    if (P.few) {
+        P.mt = 16;
+        if (fs <= 0) {  // two workgroups per CU, at least 8 blocks each
+            splits = 2 * cus / P.n_tiles;
+            if (splits > L.KB / 8) splits = L.KB / 8;
+            if (splits < 1) splits = 1;
+        }
+    } else {
+        const bool forced = tile == 32 || tile == 64 || tile == 128;
+        float best = 0.f;
+        P.mt = 0;
+        for (int t = 32; t <= 128; t *= 2) {
+            if (forced ? t != tile : (t > 32 && (M <= t / 2 || (i8 && t == 128)))) continue;
+            const int64_t base = P.n_tiles * ((M + t - 1) / t);
+            const int64_t first = fs > 0 ? splits : 1;
+            for (int64_t s = first; s == first || (fs <= 0 && s * 3 <= L.KB && base * s <= 3 * cus); ++s) {
+                const float c = mfma_cost(L, M, t, (int)s, cus);
+                if (P.mt != 0 && c >= best) continue;
+                best = c;
+                P.mt = t;
+                splits = s;
+            }
+        }
+    }
+    P.m_tiles = (M + P.mt - 1) / P.mt;
     P.kbs = (int)((L.KB + splits - 1) / splits);
     if (P.few) {  // whole passes of the kernel
         P.kbs = (P.kbs + 7) / 8 * 8;

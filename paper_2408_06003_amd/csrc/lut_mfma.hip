@@ -432,6 +432,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
         sc = s.sc;
         nsz = -(s.sc * s.zo);
     }
+    uint32_t sw = 0u;
+    if constexpr (INT8) sw = ((const uint32_t *)p.meta)[p.per_tensor ? 0 : n];
     auto finish = [&](Out y, Out S) {  // S: the row's activation sum (0 where it does not enter)
         if constexpr (INT8) return 2 * y - S * (wfmt == LUTGEMM_WFMT_TERNARY ? 2 : 1);  // as store_out expects it
         else if constexpr (!GRP) return fmaf(nsz, S, y * sc);
@@ -466,14 +468,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
                     }
                 }
             } else {
-#pragma unroll 4
-                for (int r = 0; r < rows; ++r) {
-                    const int64_t m = mr + r;
-                    const Out y = finish(ew[r * 64 + lane], zero_term ? ((const Out *)p.S)[m] : (Out)0);
-                    if (n < p.N) {
-                        const Epi ep = load_epi<INT8>(p, wfmt, m, n, false);
-                        store_out<INT8>(p, wfmt, m, n, INT8 ? 0.f : (float)y, INT8 ? (int)y : 0, ep);
+                // some rows at a time, all their operands requested before the first is used (row
+                // by row, INT8 64 x 4096 x 4096 in one range took 7 us longer); rows past the
+                // last one and columns past N repeat it and are not stored
+                const int64_t nc = n < p.N ? n : p.N - 1;
+                constexpr int GB = MS == 4 && GRP ? 4 : 8;
+#pragma unroll 1
+                for (int q = 0; q < rows; q += GB) {
+                    Out y[GB];
+                    Epi ep[GB];
+#pragma unroll
+                    for (int r = 0; r < GB; ++r) {
+                        const int rr = q + r < rows ? q + r : rows - 1;
+                        y[r] = finish(ew[rr * 64 + lane], zero_term ? ((const Out *)p.S)[mr + rr] : (Out)0);
+                        ep[r] = Epi{p.tok ? p.tok[mr + rr] : 1.f, sw, 0u, 0};
                     }
+                    if (p.accumulate && p.out_dtype == LUTGEMM_OUT_FP16) {
+#pragma unroll
+                        for (int r = 0; r < GB; ++r) ep[r].prev = ((const uint16_t *)p.out)[(mr + (q + r < rows ? q + r : rows - 1)) * p.N + nc];
+                    } else if (p.accumulate) {
+#pragma unroll
+                        for (int r = 0; r < GB; ++r) ep[r].prev = ((const uint32_t *)p.out)[(mr + (q + r < rows ? q + r : rows - 1)) * p.N + nc];
+                    }
+#pragma unroll
+                    for (int r = 0; r < GB; ++r)
+                        if (q + r < rows) store_out<INT8>(p, wfmt, mr + q + r, n, INT8 ? 0.f : (float)y[r], INT8 ? (int)y[r] : 0, ep[r]);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");

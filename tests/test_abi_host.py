@@ -312,3 +312,22 @@ def test_matrix_core_plan():
     with tuning(MFMA=0):
         ws = L.workspace_size(q8, 4096)
     assert L.workspace_size(q8, 4096) == ws
+
+
+@pytest.mark.parametrize("K,N,bits,act", [(128, 1, 4, 0), (1024, 1024, 2, 0), (4096, 4096, 2, 1), (28672, 8192, 1, 0), (2432, 11973, 2, 1)])
+def test_matrix_core_plan_sizes(K, N, bits, act):
+    """Every choice of tile and ranges, also a forced one outside the layer, has a workspace
+    that holds its partial sums: at most three workgroups per CU's worth of them."""
+    fmt = (L.WFMT_UINT, 128, L.ACT_FP16, False) if act == 0 else (L.WFMT_TERNARY, 0, L.ACT_INT8, True)
+    p = L.problem(K, N, bits, *fmt)
+    n_pad = -(-N // 256) * 256
+    for M in (3, 17, 64, 65, 129, 256, 1000, 4097):
+        rows = -(-M // 128) * 128
+        for tile, splits in ((0, 0), (32, 1000), (64, 7), (128, 0), (48, 0), (16, 3)):
+            with tuning(MFMA=1, MFMA_TILE=tile, MFMA_SPLITS=splits):
+                ws = L.workspace_size(p, M)
+            prep = rows * -(-K // 1024) * 1024 * 2 + M * max(K // 128, 1) * 8 + 65536
+            most = max(splits, 1) * rows * n_pad * 4 if splits else 3 * 256 * 128 * 256 * 4
+            with tuning(MFMA=0):
+                lookups = L.workspace_size(p, M)
+            assert ws <= max(L.WORKSPACE_ZERO_BYTES + most + prep, lookups), (M, tile, splits)
