@@ -678,7 +678,7 @@ def _call_kind(name):
         return "attach"
     if "lut_fused_" in name:
         return "fused"
-    if "lut_gemv" in name or "lut_mtok_kernel" in name:
+    if any(k in name for k in ("lut_gemv", "lut_mtok_kernel", "mfma_gemm_kernel", "mfma_few_kernel")):
         return "mpgemm"
     if "dequant_" in name:
         return "dequant"
