@@ -416,6 +416,8 @@ LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     P.kind = -1;
     const int force = tuning(LUTGEMM_TUNE_MFMA);
     if (L.act == LUTGEMM_ACT_FP16_LUT8 || L.tri || M <= 2 || force == 0) return P;
+    // these kernels' byte offsets into a tile of activations and a block of planes are 32-bit
+    if (L.K > (int64_t)1 << 22 || L.N_pad > (int64_t)1 << 24) return P;
     const bool i8 = L.act == LUTGEMM_ACT_INT8;
     // overrides of the multi-token lookup kernel select that kernel
     if (force < 0) {

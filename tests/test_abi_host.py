@@ -331,3 +331,13 @@ def test_matrix_core_plan_sizes(K, N, bits, act):
             with tuning(MFMA=0):
                 lookups = L.workspace_size(p, M)
             assert ws <= max(L.WORKSPACE_ZERO_BYTES + most + prep, lookups), (M, tile, splits)
+
+
+@pytest.mark.parametrize("K,N,act", [(1 << 23, 256, 0), (1 << 23, 256, 1), (128, (1 << 24) + 1, 1)])
+def test_matrix_core_plan_offset_limits(K, N, act):
+    """Layers whose tiles exceed 32-bit byte offsets keep the lookups."""
+    fmt = (L.WFMT_UINT, 128, L.ACT_FP16, False) if act == 0 else (L.WFMT_TERNARY, 0, L.ACT_INT8, True)
+    p = L.problem(K, N, 2, *fmt)
+    planned = L.workspace_size(p, 17)
+    with tuning(MFMA=0):
+        assert planned == L.workspace_size(p, 17)
