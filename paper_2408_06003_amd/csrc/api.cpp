@@ -416,8 +416,9 @@ LutPlan plan_mfma(const Layout &L, int64_t M, bool fused) {
     P.kind = -1;
     const int force = tuning(LUTGEMM_TUNE_MFMA);
     if (L.act == LUTGEMM_ACT_FP16_LUT8 || L.tri || M <= 2 || force == 0) return P;
-    // these kernels' byte offsets into a tile of activations and a block of planes are 32-bit
-    if (L.K > (int64_t)1 << 22 || L.N_pad > (int64_t)1 << 24) return P;
+    // these kernels' byte offsets into a tile of activations and a block of planes are 32-bit,
+    // and the preparation keeps one FP32 sum per 128-block in 64 KiB of LDS
+    static_assert(MAX_K <= int64_t(1) << 21 && MAX_N <= int64_t(1) << 24, "limits of the matrix-core kernels");
     const bool i8 = L.act == LUTGEMM_ACT_INT8;
     // overrides of the multi-token lookup kernel select that kernel
     if (force < 0) {
@@ -533,7 +534,6 @@ static lutgemm_status_t run_mfma(const Layout &L, const LutPlan &plan, int64_t M
     lp.act = (const uint16_t *)act;
     const bool i8 = L.act == LUTGEMM_ACT_INT8;
     if (plan.few) {
-        lp.act = (const uint16_t *)act;
         int e = launch_mfma_few_prep(lp, L, ws + plan.prep_off, stream);
         lp.act = (const uint16_t *)(ws + plan.prep_off);
         if (e == 0) e = launch_mfma_few(lp, L, plan, stream);

@@ -333,11 +333,11 @@ def test_matrix_core_plan_sizes(K, N, bits, act):
             assert ws <= max(L.WORKSPACE_ZERO_BYTES + most + prep, lookups), (M, tile, splits)
 
 
-@pytest.mark.parametrize("K,N,act", [(1 << 23, 256, 0), (1 << 23, 256, 1), (128, (1 << 24) + 1, 1)])
-def test_matrix_core_plan_offset_limits(K, N, act):
-    """Layers whose tiles exceed 32-bit byte offsets keep the lookups."""
+@pytest.mark.parametrize("K,N,act", [(1 << 20, 256, 0), (1 << 20, 256, 1), (128, 1 << 24, 1)])
+def test_matrix_core_plan_largest_layers(K, N, act):
+    """The largest layers that are taken have a matrix-core plan, and the next larger are
+    refused: the kernels' 32-bit offsets and block sums in LDS hold for all that are planned."""
     fmt = (L.WFMT_UINT, 128, L.ACT_FP16, False) if act == 0 else (L.WFMT_TERNARY, 0, L.ACT_INT8, True)
-    p = L.problem(K, N, 2, *fmt)
-    planned = L.workspace_size(p, 17)
-    with tuning(MFMA=0):
-        assert planned == L.workspace_size(p, 17)
+    assert L.workspace_size(L.problem(K, N, 2, *fmt), 17) > 0
+    larger = (K + 128, N) if K > 128 else (K, N + 1)
+    assert L.workspace_size(L.problem(*larger, 2, *fmt), 17) == 0
